@@ -63,7 +63,9 @@ enum {
 /* CNN arithmetic precision for cnnsns_predict / the serving loop. */
 enum {
     CNNSNS_F32 = 0,     /* FP32 operands and activations, FP32 accumulation (the 32 -> 32 layers
-                           as Winograd F(2x2,3x3) contractions: within 1e-5 of the exact result) */
+                           as minimal-filtering (Winograd) contractions, on the FP32 matrix
+                           instruction or with every operand as three BF16 values that add up
+                           to it: within 1e-5 of the exact result) */
     CNNSNS_BF16 = 1,    /* BF16 operands and activations, FP32 accumulation */
     CNNSNS_FP8E4M3 = 2, /* FP8 e4m3 (OCP: 3 mantissa bits, largest finite 448) operands with
                            FP32 accumulation: a power-of-two scale per layer and output channel
@@ -135,7 +137,8 @@ int cnnsns_destroy_mesh(cnnsns_mesh m);
  *   disp  DEVICE FP32 [2][G][G] output (caller-owned): predicted (dx, dy).
  * The mesh keeps a workspace for the forward pass, allocated on first use and
  * grown when needed (FP32: one 32-channel FP32 activation of 128 G^2 bytes
- * plus 128 KiB of transformed weights; BF16: 40 KiB of packed weights; FP8:
+ * plus up to 161 KiB of prepared weights and 16 G (ceil(G / 256) - 1) bytes of sums
+ * that column strips exchange; BF16: 40 KiB of packed weights; FP8:
  * 20 KiB of packed weights and 2 KiB of scales) until it is destroyed.
  * FP8: the weight scale of output channel o of a layer is the smallest power of
  * two s with max|w_o| / s <= 448; the velocity's is that of max|u, v| over the

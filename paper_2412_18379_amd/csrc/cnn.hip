@@ -4,8 +4,9 @@
 // with the overlay velocity).  Cross-correlation with OIHW weights:
 //   y[o][r][c] = b[o] + sum_i sum_{dy,dx} w[o][i][dy+1][dx+1] x[i][r+dy][c+dx].
 //
-// Two fused FP32 kernels per forward pass, both persistent (one block per
-// compute unit) looping over tiles:
+// The FP32 pass has two forms.  Mid-sized overlays take the tile form, the rest
+// the row-streaming form of cnn_rows.h (rows_form below).  The tile form is two
+// fused kernels, both persistent (one block per compute unit) looping over tiles:
 //   conv12: 8 wavefronts, two per SIMD, each owning one row of conv2's 2 x 2
 //           output blocks (under 256 registers each): conv1 (K = 18 padded
 //           to 20) on the matrix cores into LDS on the 16 x 32 tile plus a
@@ -31,13 +32,12 @@
 // stride, so a lane fetches 4 channels of one pixel with one 16-byte read.
 // The next tile's input is fetched into registers while the current tile
 // computes.
+#include "cnn_rows.h"
 #include "common.h"
 #include "strip.h"
 
 namespace cnnsns {
 namespace {
-
-typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int RH = 16, RW = 32;          // MFMA region per block
 constexpr int IH = RH + 2, IW = RW + 2;  // its input tile (one-pixel border)
@@ -80,10 +80,16 @@ static_assert(RW == 32, "a row of 2 x 2 output blocks is one 16-row matrix block
 // u[(((xn * 2 + nb) * 2 + h) * 64 + l) * 4 + j] holds
 //   U[xn = 4 xi + nu][output channel 16 nb + l%16][input channel 8 (l/16) + 4h + j],
 // so a lane reads the A operands of four k-steps as one float4.
-__global__ void k_wino_weights(const float* __restrict__ w, float* __restrict__ u)
+// Both layers in one launch: u holds the second layer's NU values after the first's.
+__global__ void k_wino_weights(const float* __restrict__ w2, const float* __restrict__ w3, float* __restrict__ u)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= NU) return;
+    int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= 2 * NU) return;
+    const float* w = k < NU ? w2 : w3;
+    if (k >= NU) {
+        k -= NU;
+        u += NU;
+    }
     const int j = k & 3, l = (k >> 2) & 63, h = (k >> 8) & 1, nb = (k >> 9) & 1, xn = k >> 10;
     const int xi = xn >> 2, nu = xn & 3;
     const int o = nb * 16 + (l & 15), ci = 8 * (l >> 4) + 4 * h + j;
@@ -691,12 +697,18 @@ inline unsigned cdiv(int64_t a, int64_t b)
     return (unsigned)((a + b - 1) / b);
 }
 
-// One block per compute unit (the LDS footprint allows one), a multiple of the 8 XCDs.
-unsigned persistent_grid(int ntiles)
+int compute_units()
 {
     int dev = 0, cus = 0;
     hip_check(hipGetDevice(&dev), "hipGetDevice");
     hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "CU count");
+    return cus;
+}
+
+// One block per compute unit (the LDS footprint allows one), a multiple of the 8 XCDs.
+unsigned persistent_grid(int ntiles)
+{
+    const int cus = compute_units();
     int g = cus < ntiles ? cus : ntiles;
     g = (g + 7) / 8 * 8;
     return (unsigned)(g < 8 ? 8 : g);
@@ -709,10 +721,21 @@ unsigned cnn_persistent_grid()
     return persistent_grid(1 << 30);
 }
 
+// Which form of the FP32 pass runs.  A row block pays for its weights and halo rows, three to five rows'
+// worth, so the row form loses where its segments are a few rows long; below that, at one row a segment,
+// the tile form's single tile for a part of the compute units takes longer.  Kernels of a pass in us, tile and
+// row form: G = 33: 40.8 and 35.9, 128: 41.8 and 38.8, 160: 42.2 and 49.1, 512: 93 and 98, 700: 152 and 147,
+// 800: 181 and 187, 900: 239 and 210, 1024: 283 and 236, 1531: 583 and 495.
+static bool rows_form(int32_t G)
+{
+    return G <= 128 || G >= 832;
+}
+
 size_t cnn_workspace_bytes(int32_t G, int32_t precision)
 {
     if (precision == CNNSNS_BF16) return cnn_bf16_workspace_bytes();
     if (precision == CNNSNS_FP8E4M3) return cnn_fp8_workspace_bytes();
+    if (rows_form(G)) return rows::workspace_bytes(G);
     return sizeof(float) * (2 * (size_t)NU + (size_t)C * (size_t)G * (size_t)G);
 }
 
@@ -729,11 +752,15 @@ void run_cnn(int32_t G, const float* vel, const cnnsns_cnn& w, int32_t precision
         return;
     }
     if (precision != CNNSNS_F32) fail(CNNSNS_EINVAL, "predict: unknown precision");
+    if (rows_form(G)) {
+        rows::forward(G, vel, w, disp, ws, compute_units(), stream);
+        hip_check(hipGetLastError(), "predict launch");
+        return;
+    }
     float* u2 = static_cast<float*>(ws);
     float* u3 = u2 + NU;
     float* act2 = u3 + NU;
-    k_wino_weights<<<cdiv(NU, 256), 256, 0, stream>>>(w.w[1], u2);
-    k_wino_weights<<<cdiv(NU, 256), 256, 0, stream>>>(w.w[2], u3);
+    k_wino_weights<<<cdiv(2 * NU, 256), 256, 0, stream>>>(w.w[1], w.w[2], u2);
     const int tx12 = (int)cdiv(G, RW), n12 = tx12 * (int)cdiv(G, RH);
     const int tx34 = (int)cdiv(G, OW34);
     int n34 = 0;
