@@ -193,7 +193,7 @@ __global__ void k3c_wprep4_bf16(const float* __restrict__ w, bf16x8* __restrict_
 }
 
 // Layers 2-4 of the BF16 pass as z-sweeps through LDS.  A block owns a column of ZY x ZX cells
-// and ZP consecutive planes; it keeps the three input planes that its current output plane reads,
+// and zp consecutive planes (z_planes below); it keeps the three input planes that its current output plane reads,
 // each as a (ZY + 2) x (ZX + 2) slab with the one-cell border (zero outside the grid), in a ring
 // in LDS, so every input cell is read from memory once per block (plus the borders) instead of
 // once per tap.  While a plane's 27 taps run on the matrix cores, the plane after next is loaded
@@ -201,7 +201,7 @@ __global__ void k3c_wprep4_bf16(const float* __restrict__ w, bf16x8* __restrict_
 // 16-cell M-blocks each (the 256 cells of a plane; sixteen wavefronts of one M-block each ran
 // 10% slower); a tap is one v_mfma_f32_16x16x32_bf16 per M-block and 16 output channels (NB such
 // blocks: two for 32 -> 32, one for 32 -> 3 with the outputs padded to 16).
-constexpr int ZY = 8, ZX = 32, ZP = 32;           // cells per block: rows, columns, planes
+constexpr int ZY = 8, ZX = 32;                    // cells per block: rows, columns
 constexpr int ZSY = ZY + 2, ZSX = ZX + 2;         // slab with its border
 // bf16 per slab cell: 32 channels + 16 pad, 96 bytes.  The LDS serves a 16-byte read in groups of
 // 16 lanes over 64 four-byte banks, a group joining lanes 0-7 with 56-63 (8-15 with 48-55, ...): here
@@ -216,7 +216,7 @@ static_assert(ZY * ZX == (kZThreads / 64) * 2 * 16, "two M-blocks per wavefront 
 
 template <int NB>
 __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k3c_zsweep_bf16(
-    int32_t G, const bf16* __restrict__ in, const bf16x8* __restrict__ wb, const float* __restrict__ bias,
+    int32_t G, int zp, const bf16* __restrict__ in, const bf16x8* __restrict__ wb, const float* __restrict__ bias,
     bf16* __restrict__ out, float* __restrict__ disp)
 {
     __shared__ __attribute__((aligned(16))) bf16 s_slab[3 * ZSLAB];
@@ -227,8 +227,8 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2)
     const int tiles_x = (G + ZX - 1) / ZX, tiles_y = (G + ZY - 1) / ZY;
     const int64_t b = blockIdx.x;
     const int tx0 = (int)(b % tiles_x) * ZX, ty0 = (int)((b / tiles_x) % tiles_y) * ZY;
-    const int z0 = (int)(b / ((int64_t)tiles_x * tiles_y)) * ZP;
-    const int z1 = min(z0 + ZP, G);
+    const int z0 = (int)(b / ((int64_t)tiles_x * tiles_y)) * zp;
+    const int z1 = min(z0 + zp, G);
     const int64_t GG = (int64_t)G * G;
 
     // the wavefront's M-blocks: cells (ty0 + r, tx0 + 16 h + col) with r = wave, h = 0, 1
@@ -347,7 +347,7 @@ constexpr int Z1CS = 4;  // floats per slab cell
 
 constexpr int kZ1Threads = 1024;  // one 16-cell M-block per wavefront
 template <class T>
-__global__ __launch_bounds__(kZ1Threads) void k3c_zconv1(int32_t G, const float* __restrict__ vel,
+__global__ __launch_bounds__(kZ1Threads) void k3c_zconv1(int32_t G, int zp, const float* __restrict__ vel,
                                                         const float* __restrict__ w, const float* __restrict__ bias,
                                                         T* __restrict__ out)
 {
@@ -365,8 +365,8 @@ __global__ __launch_bounds__(kZ1Threads) void k3c_zconv1(int32_t G, const float*
     const int tiles_x = (G + ZX - 1) / ZX, tiles_y = (G + ZY - 1) / ZY;
     const int64_t b = blockIdx.x;
     const int tx0 = (int)(b % tiles_x) * ZX, ty0 = (int)((b / tiles_x) % tiles_y) * ZY;
-    const int z0 = (int)(b / ((int64_t)tiles_x * tiles_y)) * ZP;
-    const int z1 = min(z0 + ZP, G);
+    const int z0 = (int)(b / ((int64_t)tiles_x * tiles_y)) * zp;
+    const int z1 = min(z0 + zp, G);
     const int64_t GG = (int64_t)G * G, n = GG * G;
     const int r = wave >> 1, h = wave & 1;
 
@@ -460,7 +460,7 @@ __global__ void k3c_wprep1_split(const float* __restrict__ w, bf16x8* __restrict
     wb[k] = v;
 }
 
-__global__ __launch_bounds__(kZ1Threads) void k3c_zconv1_split(int32_t G, const float* __restrict__ vel,
+__global__ __launch_bounds__(kZ1Threads) void k3c_zconv1_split(int32_t G, int zp, const float* __restrict__ vel,
                                                                const bf16x8* __restrict__ wb,
                                                                const float* __restrict__ bias, bf16* __restrict__ out)
 {
@@ -475,8 +475,8 @@ __global__ __launch_bounds__(kZ1Threads) void k3c_zconv1_split(int32_t G, const 
     const int tiles_x = (G + ZX - 1) / ZX, tiles_y = (G + ZY - 1) / ZY;
     const int64_t b = blockIdx.x;
     const int tx0 = (int)(b % tiles_x) * ZX, ty0 = (int)((b / tiles_x) % tiles_y) * ZY;
-    const int z0 = (int)(b / ((int64_t)tiles_x * tiles_y)) * ZP;
-    const int z1 = min(z0 + ZP, G);
+    const int z0 = (int)(b / ((int64_t)tiles_x * tiles_y)) * zp;
+    const int z1 = min(z0 + zp, G);
     const int64_t GG = (int64_t)G * G, n = GG * G;
     const int r = wave >> 1, h = wave & 1;
 
@@ -540,12 +540,12 @@ __global__ __launch_bounds__(kZ1Threads) void k3c_zconv1_split(int32_t G, const 
 }
 
 // Layer 4 of the FP32 pass (32 -> 3) as a z-sweep on the vector ALUs: a block owns a column of
-// Z4Y x Z4X cells (one per thread) and Z4P output planes, and reads each input plane once, as one
+// Z4Y x Z4X cells (one per thread) and zp output planes, and reads each input plane once, as one
 // slab with its one-cell border in LDS.  An input plane p feeds output planes p + 1, p and p - 1
 // (kernel depth index 0, 1, 2), so a thread keeps the partial sums of three output planes; after
 // plane p, output plane p - 1 is complete and written.  The weights are uniform across the block
 // (scalar loads); the next plane's slab is loaded into registers while this one is used.
-constexpr int Z4Y = 8, Z4X = 64, Z4P = 16;
+constexpr int Z4Y = 8, Z4X = 64;
 constexpr int Z4SY = Z4Y + 2, Z4SX = Z4X + 2;
 constexpr int Z4CS = C + 4;  // floats per slab cell (32 channels + 4 pad)
 constexpr int kZ4Threads = Z4Y * Z4X;
@@ -562,7 +562,7 @@ __global__ void k3c_wprep4_f32(const float* __restrict__ w, float* __restrict__ 
     w4t[k] = w[(o * C + ci) * TAPS + d * 9 + t9];
 }
 
-__global__ __launch_bounds__(kZ4Threads) void k3c_zconv4_f32(int32_t G, const float* __restrict__ in,
+__global__ __launch_bounds__(kZ4Threads) void k3c_zconv4_f32(int32_t G, int zp, const float* __restrict__ in,
                                                               const float* __restrict__ w,
                                                               const float* __restrict__ bias, float* __restrict__ disp)
 {
@@ -571,8 +571,8 @@ __global__ __launch_bounds__(kZ4Threads) void k3c_zconv4_f32(int32_t G, const fl
     const int tiles_x = (G + Z4X - 1) / Z4X, tiles_y = (G + Z4Y - 1) / Z4Y;
     const int64_t b = blockIdx.x;
     const int tx0 = (int)(b % tiles_x) * Z4X, ty0 = (int)((b / tiles_x) % tiles_y) * Z4Y;
-    const int z0 = (int)(b / ((int64_t)tiles_x * tiles_y)) * Z4P;
-    const int z1 = min(z0 + Z4P, G);
+    const int z0 = (int)(b / ((int64_t)tiles_x * tiles_y)) * zp;
+    const int z1 = min(z0 + zp, G);
     const int64_t GG = (int64_t)G * G, n = GG * G;
     const int r = tid / Z4X, c = tid % Z4X;
     const int gy = ty0 + r, gx = tx0 + c;
@@ -645,6 +645,29 @@ __global__ __launch_bounds__(kZ4Threads) void k3c_zconv4_f32(int32_t G, const fl
     }
 }
 
+// Planes per block of a z-sweep over `tiles` columns, `slots` blocks running at once: the length that makes
+// the busiest place's planes fewest, a block costing about three planes besides its own (its weights and the two
+// planes before its first).  With 32 planes whatever the overlay, small ones ran as a handful of long
+// blocks: the FP32 pass took 0.46 ms at G = 32 as at G = 64, and the BF16 pass 304 us at G = 101, whose fourth
+// segment had 5 planes.
+inline int z_planes(int G, int64_t tiles, int slots)
+{
+    int best = G;
+    int64_t cost = -1;
+    for (int r = 1; r <= 4; ++r) {
+        int64_t segs = tiles < (int64_t)r * slots ? (int64_t)r * slots / tiles : 1;
+        if (segs > G) segs = G;
+        const int zp = (int)((G + segs - 1) / segs);
+        segs = (G + zp - 1) / zp;
+        const int64_t c = (tiles * segs + slots - 1) / slots * (zp + 3);
+        if (cost < 0 || c < cost) {
+            cost = c;
+            best = zp;
+        }
+    }
+    return best;
+}
+
 }  // namespace
 
 size_t cnn3_workspace_bytes(int32_t G)
@@ -662,7 +685,9 @@ void run_predict3(cnnsns_mesh3_s& m, const float* vel, const cnnsns_cnn& w, int3
     const int32_t G = m.G;
     const int64_t cells = (int64_t)G * G * G;
     const unsigned grid = cnn_persistent_grid();
-    const int64_t zblocks = (int64_t)((G + ZX - 1) / ZX) * ((G + ZY - 1) / ZY) * ((G + ZP - 1) / ZP);
+    const int64_t ztiles = (int64_t)((G + ZX - 1) / ZX) * ((G + ZY - 1) / ZY);
+    const int zp = z_planes(G, ztiles, (int)grid);
+    const int64_t zblocks = ztiles * ((G + zp - 1) / zp);
     if (zblocks > (int64_t)UINT32_MAX) fail(CNNSNS_EINVAL, "predict3d: overlay too large");
     float* act0 = static_cast<float*>(m.ws.ptr);
     float* act1 = act0 + cells * C;
@@ -677,23 +702,25 @@ void run_predict3(cnnsns_mesh3_s& m, const float* vel, const cnnsns_cnn& w, int3
         k3c_wprep_bf16<<<(NWB + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[2], wb3);
         bf16x8* wb1 = wb2 + NWB;  // after layer 2's operands in their 108 KiB region
         k3c_wprep1_split<<<(NW1S + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[0], wb1);
-        k3c_zconv1_split<<<(unsigned)zblocks, kZ1Threads, 0, stream>>>(G, vel, wb1, w.b[0], b0);
-        k3c_zsweep_bf16<2><<<(unsigned)zblocks, kZThreads, 0, stream>>>(G, b0, wb2, w.b[1], b1, nullptr);
-        k3c_zsweep_bf16<2><<<(unsigned)zblocks, kZThreads, 0, stream>>>(G, b1, wb3, w.b[2], b0, nullptr);
+        k3c_zconv1_split<<<(unsigned)zblocks, kZ1Threads, 0, stream>>>(G, zp, vel, wb1, w.b[0], b0);
+        k3c_zsweep_bf16<2><<<(unsigned)zblocks, kZThreads, 0, stream>>>(G, zp, b0, wb2, w.b[1], b1, nullptr);
+        k3c_zsweep_bf16<2><<<(unsigned)zblocks, kZThreads, 0, stream>>>(G, zp, b1, wb3, w.b[2], b0, nullptr);
         bf16x8* wb4 = wb3 + NWB;
         k3c_wprep4_bf16<<<(TAPS * 64 + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[3], wb4);
-        k3c_zsweep_bf16<1><<<(unsigned)zblocks, kZThreads, 0, stream>>>(G, b0, wb4, w.b[3], nullptr, disp);
+        k3c_zsweep_bf16<1><<<(unsigned)zblocks, kZThreads, 0, stream>>>(G, zp, b0, wb4, w.b[3], nullptr, disp);
     } else {
         k3c_wprep<<<(NWT + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[1], wt2);
         k3c_wprep<<<(NWT + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[2], wt3);
-        k3c_zconv1<float><<<(unsigned)zblocks, kZ1Threads, 0, stream>>>(G, vel, w.w[0], w.b[0], act0);
+        k3c_zconv1<float><<<(unsigned)zblocks, kZ1Threads, 0, stream>>>(G, zp, vel, w.w[0], w.b[0], act0);
         k3c_conv32<<<grid, kWaves32 * 64, 0, stream>>>(G, act0, wt2, w.b[1], act1);
         k3c_conv32<<<grid, kWaves32 * 64, 0, stream>>>(G, act1, wt3, w.b[2], act0);
-        const int64_t z4blocks = (int64_t)((G + Z4X - 1) / Z4X) * ((G + Z4Y - 1) / Z4Y) * ((G + Z4P - 1) / Z4P);
+        const int64_t z4tiles = (int64_t)((G + Z4X - 1) / Z4X) * ((G + Z4Y - 1) / Z4Y);
+        const int z4p = z_planes(G, z4tiles, (int)grid);
+        const int64_t z4blocks = z4tiles * ((G + z4p - 1) / z4p);
         if (z4blocks > (int64_t)UINT32_MAX) fail(CNNSNS_EINVAL, "predict3d: overlay too large");
         float* w4t = wt3 + NWT;
         k3c_wprep4_f32<<<(TAPS * C * CIO + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[3], w4t);
-        k3c_zconv4_f32<<<(unsigned)z4blocks, kZ4Threads, 0, stream>>>(G, act0, w4t, w.b[3], disp);
+        k3c_zconv4_f32<<<(unsigned)z4blocks, kZ4Threads, 0, stream>>>(G, z4p, act0, w4t, w.b[3], disp);
     }
     hip_check(hipGetLastError(), "predict3d launch");
     workspace_used(m.ws, stream);
