@@ -49,10 +49,8 @@ constexpr int kWaves32 = 12;      // matrix layers: waves per block (three per S
 constexpr int kSeg = 64;          // cells per wavefront work item (four 16-cell blocks)
 
 // wt[((tap * 2 + nb) * 2 + h) * 64 + l) * 4 + j] = W[16 nb + l%16][8 (l/16) + 4h + j][tap]
-__global__ void k3c_wprep(const float* __restrict__ w, float* __restrict__ wt)
+__device__ __forceinline__ void wprep(int k, const float* __restrict__ w, float* __restrict__ wt)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= NWT) return;
     const int j = k & 3, l = (k >> 2) & 63, h = (k >> 8) & 1, nb = (k >> 9) & 1, tap = k >> 10;
     const int o = 16 * nb + (l & 15), ci = 8 * (l >> 4) + 4 * h + j;
     wt[k] = w[(o * C + ci) * TAPS + tap];
@@ -164,10 +162,8 @@ __global__ __launch_bounds__(kWaves32 * 64) void k3c_conv32(int32_t G, const flo
 // BF16 operand-ordered weights: wb[(tap * 2 + nb) * 64 + l] holds, as 8 BF16 (rounded to
 // nearest even), W[16 nb + l%16][8 (l/16) + j][tap] for j = 0..7: the A operand of
 // v_mfma_f32_16x16x32_bf16 (row = output channel, k = input channel 8 (l/16) + j).
-__global__ void k3c_wprep_bf16(const float* __restrict__ w, bf16x8* __restrict__ wb)
+__device__ __forceinline__ void wprep_bf16(int k, const float* __restrict__ w, bf16x8* __restrict__ wb)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= NWB) return;
     const int l = k & 63, nb = (k >> 6) & 1, tap = k >> 7;
     const int o = 16 * nb + (l & 15), c0 = 8 * (l >> 4);
     v8f v;
@@ -180,10 +176,8 @@ __global__ void k3c_wprep_bf16(const float* __restrict__ w, bf16x8* __restrict__
 // block, wb4[tap * 64 + l] = W4[l%16][8 (l/16) + j][tap] as BF16 (zero for rows >= 3), so a tap is
 // one v_mfma_f32_16x16x32_bf16 per 16 cells; lanes 0..15 receive output channels 0..3 of their
 // cell, the first three of which are written with the bias added.
-__global__ void k3c_wprep4_bf16(const float* __restrict__ w, bf16x8* __restrict__ wb)
+__device__ __forceinline__ void wprep4_bf16(int k, const float* __restrict__ w, bf16x8* __restrict__ wb)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= TAPS * 64) return;
     const int l = k & 63, tap = k >> 6;
     const int o = l & 15, c0 = 8 * (l >> 4);
     v8f v;
@@ -436,10 +430,8 @@ __global__ __launch_bounds__(kZ1Threads) void k3c_zconv1(int32_t G, int zp, cons
 constexpr int NW1S = 14 * 2 * 64;  // bf16x8 operands of the split layer 1
 
 // wb[(s * 2 + nb) * 64 + l]: output channel 16 nb + l%16; lane group g = l/16 takes tap 2 s + g/2
-__global__ void k3c_wprep1_split(const float* __restrict__ w, bf16x8* __restrict__ wb)
+__device__ __forceinline__ void wprep1_split(int k, const float* __restrict__ w, bf16x8* __restrict__ wb)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= NW1S) return;
     const int l = k & 63, nb = (k >> 6) & 1, st = k >> 7, g = l >> 4;
     const int o = 16 * nb + (l & 15), t = 2 * st + (g >> 1);
     bf16x8 v = bf16x8{ 0, 0, 0, 0, 0, 0, 0, 0 };
@@ -554,10 +546,8 @@ constexpr int Z4CH_PER_THREAD = (Z4CHUNKS + kZ4Threads - 1) / kZ4Threads;
 
 // w4t[(t9 * C + ci) * 9 + d * 3 + o] = W4[o][ci][d * 9 + t9]: for one (dy, dx) the 288 weights
 // of all channels, depths and outputs are contiguous (scalar loads of whole lines)
-__global__ void k3c_wprep4_f32(const float* __restrict__ w, float* __restrict__ w4t)
+__device__ __forceinline__ void wprep4_f32(int k, const float* __restrict__ w, float* __restrict__ w4t)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= TAPS * C * CIO) return;
     const int o = k % 3, d = (k / 3) % 3, ci = (k / 9) % C, t9 = k / (9 * C);
     w4t[k] = w[(o * C + ci) * TAPS + d * 9 + t9];
 }
@@ -645,6 +635,30 @@ __global__ __launch_bounds__(kZ4Threads) void k3c_zconv4_f32(int32_t G, int zp, 
     }
 }
 
+// All operand-ordered weights of a pass in one launch (each launch of them took 4.2 us, of a 44 us pass
+// at G = 16).
+__global__ void k3c_prep_bf16(const float* __restrict__ w1, const float* __restrict__ w2, const float* __restrict__ w3,
+                              const float* __restrict__ w4, bf16x8* __restrict__ wb1, bf16x8* __restrict__ wb2,
+                              bf16x8* __restrict__ wb3, bf16x8* __restrict__ wb4)
+{
+    int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < NWB) return wprep_bf16(k, w2, wb2);
+    if ((k -= NWB) < NWB) return wprep_bf16(k, w3, wb3);
+    if ((k -= NWB) < NW1S) return wprep1_split(k, w1, wb1);
+    if ((k -= NW1S) < TAPS * 64) wprep4_bf16(k, w4, wb4);
+}
+constexpr int kPrepBf16 = 2 * NWB + NW1S + TAPS * 64;
+
+__global__ void k3c_prep_f32(const float* __restrict__ w2, const float* __restrict__ w3, const float* __restrict__ w4,
+                             float* __restrict__ wt2, float* __restrict__ wt3, float* __restrict__ w4t)
+{
+    int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < NWT) return wprep(k, w2, wt2);
+    if ((k -= NWT) < NWT) return wprep(k, w3, wt3);
+    if ((k -= NWT) < TAPS * C * CIO) wprep4_f32(k, w4, w4t);
+}
+constexpr int kPrepF32 = 2 * NWT + TAPS * C * CIO;
+
 // Planes per block of a z-sweep over `tiles` columns, `slots` blocks running at once: the length that makes
 // the busiest place's planes fewest, a block costing about three planes besides its own (its weights and the two
 // planes before its first).  With 32 planes whatever the overlay, small ones ran as a handful of long
@@ -698,19 +712,17 @@ void run_predict3(cnnsns_mesh3_s& m, const float* vel, const cnnsns_cnn& w, int3
         bf16* b1 = reinterpret_cast<bf16*>(act1);
         bf16x8* wb2 = reinterpret_cast<bf16x8*>(wt2);
         bf16x8* wb3 = reinterpret_cast<bf16x8*>(wt3);
-        k3c_wprep_bf16<<<(NWB + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[1], wb2);
-        k3c_wprep_bf16<<<(NWB + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[2], wb3);
-        bf16x8* wb1 = wb2 + NWB;  // after layer 2's operands in their 108 KiB region
-        k3c_wprep1_split<<<(NW1S + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[0], wb1);
+        bf16x8* wb1 = wb2 + NWB;  // after layer 2's operands in their 108 KiB region, and layer 4's after layer 3's
+        bf16x8* wb4 = wb3 + NWB;
+        k3c_prep_bf16<<<(kPrepBf16 + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[0], w.w[1], w.w[2], w.w[3], wb1, wb2,
+                                                                              wb3, wb4);
         k3c_zconv1_split<<<(unsigned)zblocks, kZ1Threads, 0, stream>>>(G, zp, vel, wb1, w.b[0], b0);
         k3c_zsweep_bf16<2><<<(unsigned)zblocks, kZThreads, 0, stream>>>(G, zp, b0, wb2, w.b[1], b1, nullptr);
         k3c_zsweep_bf16<2><<<(unsigned)zblocks, kZThreads, 0, stream>>>(G, zp, b1, wb3, w.b[2], b0, nullptr);
-        bf16x8* wb4 = wb3 + NWB;
-        k3c_wprep4_bf16<<<(TAPS * 64 + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[3], wb4);
         k3c_zsweep_bf16<1><<<(unsigned)zblocks, kZThreads, 0, stream>>>(G, zp, b0, wb4, w.b[3], nullptr, disp);
     } else {
-        k3c_wprep<<<(NWT + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[1], wt2);
-        k3c_wprep<<<(NWT + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[2], wt3);
+        float* w4t = wt3 + NWT;
+        k3c_prep_f32<<<(kPrepF32 + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[1], w.w[2], w.w[3], wt2, wt3, w4t);
         k3c_zconv1<float><<<(unsigned)zblocks, kZ1Threads, 0, stream>>>(G, zp, vel, w.w[0], w.b[0], act0);
         k3c_conv32<<<grid, kWaves32 * 64, 0, stream>>>(G, act0, wt2, w.b[1], act1);
         k3c_conv32<<<grid, kWaves32 * 64, 0, stream>>>(G, act1, wt3, w.b[2], act0);
@@ -718,8 +730,6 @@ void run_predict3(cnnsns_mesh3_s& m, const float* vel, const cnnsns_cnn& w, int3
         const int z4p = z_planes(G, z4tiles, (int)grid);
         const int64_t z4blocks = z4tiles * ((G + z4p - 1) / z4p);
         if (z4blocks > (int64_t)UINT32_MAX) fail(CNNSNS_EINVAL, "predict3d: overlay too large");
-        float* w4t = wt3 + NWT;
-        k3c_wprep4_f32<<<(TAPS * C * CIO + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[3], w4t);
         k3c_zconv4_f32<<<(unsigned)z4blocks, kZ4Threads, 0, stream>>>(G, z4p, act0, w4t, w.b[3], disp);
     }
     hip_check(hipGetLastError(), "predict3d launch");
