@@ -331,7 +331,7 @@ int cnnsns_destroy_mesh3d(cnnsns_mesh3 m);
  *              FP32 accumulation; layer 1 writes BF16 activations and layer 4
  *              reads them, both computing in FP32.  CNNSNS_FP8E4M3: EINVAL.
  *   disp  FP32 [3][G][G][G] out: the predicted displacement per cell.
- * Uses a workspace of the mesh (2 G^3 x 32 FP32 activations plus 216 KiB),
+ * Uses a workspace of the mesh (2 G^3 x 32 FP32 activations plus 342 KiB),
  * allocated on the first call; a pass is ordered on the device after the
  * previous pass on that mesh, also across streams.
  * Asynchronous on `stream`.  Errors: EINVAL (null argument, precision not

@@ -29,135 +29,21 @@
 #include <mutex>
 
 #include "common.h"
+#include "split.h"
 
 namespace cnnsns {
 namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float v8f __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16;
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int C = 32;             // hidden channels
 constexpr int CIO = 3;            // velocity / displacement components
 constexpr int TAPS = 27;
-constexpr int NWT = TAPS * 4 * 64 * 4;  // operand-ordered weights of one 32 -> 32 layer (floats)
-constexpr int NWB = TAPS * 2 * 64;      // the same in BF16 (bf16x8 entries)
-constexpr int kBlock = 256;       // vector-ALU layers
-constexpr int kWaves32 = 12;      // matrix layers: waves per block (three per SIMD, at most 170 registers)
-constexpr int kSeg = 64;          // cells per wavefront work item (four 16-cell blocks)
-
-// wt[((tap * 2 + nb) * 2 + h) * 64 + l) * 4 + j] = W[16 nb + l%16][8 (l/16) + 4h + j][tap]
-__device__ __forceinline__ void wprep(int k, const float* __restrict__ w, float* __restrict__ wt)
-{
-    const int j = k & 3, l = (k >> 2) & 63, h = (k >> 8) & 1, nb = (k >> 9) & 1, tap = k >> 10;
-    const int o = 16 * nb + (l & 15), ci = 8 * (l >> 4) + 4 * h + j;
-    wt[k] = w[(o * C + ci) * TAPS + tap];
-}
-
-// The work items (64 cells of an x row) of a persistent block: the blocks of one XCD (block id
-// mod 8) take neighbouring contiguous ranges, so the rows above and below and the neighbouring
-// planes, which the taps read, are shared in that XCD's L2.
-__device__ __forceinline__ void item_range(int64_t n_items, int64_t& i0, int64_t& i1)
-{
-    const int64_t nblk = gridDim.x;
-    int64_t lb = blockIdx.x;
-    if (nblk % 8 == 0) lb = (blockIdx.x % 8) * (nblk / 8) + blockIdx.x / 8;
-    const int64_t per = (n_items + nblk - 1) / nblk;
-    i0 = lb * per;
-    i1 = i0 + per < n_items ? i0 + per : n_items;
-}
-
-// Layers 2 and 3: 32 -> 32 with ReLU on the matrix cores, persistent blocks of 12 wavefronts
-// (three per SIMD).  The next tap's activations are loaded while this tap's 64 matrix
-// instructions run: that needs 160 registers, so three wavefronts per SIMD instead of four
-// without the prefetch (whole pass at G = 128: 3.43 ms without it, 3.25 ms with it at two
-// wavefronts per SIMD, 3.12 ms at three; four wavefronts with the prefetch spill).
-__global__ __launch_bounds__(kWaves32 * 64) void k3c_conv32(int32_t G, const float* __restrict__ in,
-                                                            const float* __restrict__ wt,
-                                                            const float* __restrict__ bias,
-                                                            float* __restrict__ out)
-{
-    __shared__ v4f s_w[NWT / 4];
-    for (int k = threadIdx.x; k < NWT / 4; k += kWaves32 * 64) s_w[k] = reinterpret_cast<const v4f*>(wt)[k];
-    __syncthreads();
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int col = lane & 15, grp = lane >> 4;
-    const int segs = (G + kSeg - 1) / kSeg;
-    const int64_t n_items = (int64_t)G * G * segs;
-    int64_t i0, i1;
-    item_range(n_items, i0, i1);
-    v4f bv[2];
-    bv[0] = *reinterpret_cast<const v4f*>(bias + 4 * grp);
-    bv[1] = *reinterpret_cast<const v4f*>(bias + 16 + 4 * grp);
-    for (int64_t item = i0 + wave; item < i1; item += kWaves32) {
-        const int seg = (int)(item % segs);
-        const int64_t row = item / segs;  // z G + y
-        const int y = (int)(row % G), z = (int)(row / G);
-        const int x0 = seg * kSeg;
-        v4f acc[4][2];
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
-            acc[mb][0] = bv[0];
-            acc[mb][1] = bv[1];
-        }
-        auto load = [&](int t, v4f (&bo)[4][2]) {
-            const int Z = z + t / 9 - 1, Y = y + (t / 3) % 3 - 1, dx = t % 3 - 1;
-            const bool ok = Z >= 0 && Z < G && Y >= 0 && Y < G;
-            const float* src = in + ((int64_t)(ok ? Z : 0) * G + (ok ? Y : 0)) * G * C + 8 * grp;
-#pragma unroll
-            for (int mb = 0; mb < 4; ++mb) {
-                const int X = x0 + 16 * mb + col + dx;
-                if (ok && X >= 0 && X < G) {
-                    const v4f* p = reinterpret_cast<const v4f*>(src + (int64_t)X * C);
-                    bo[mb][0] = p[0];
-                    bo[mb][1] = p[1];
-                } else {
-                    bo[mb][0] = v4f{ 0.f, 0.f, 0.f, 0.f };
-                    bo[mb][1] = v4f{ 0.f, 0.f, 0.f, 0.f };
-                }
-            }
-        };
-        v4f bop[4][2], bnx[4][2];
-        load(0, bop);
-        for (int t = 0; t < TAPS; ++t) {
-            if (t + 1 < TAPS) load(t + 1, bnx);
-            v4f aop[2][2];
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) aop[nb][h] = s_w[((t * 2 + nb) * 2 + h) * 64 + lane];
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-                        for (int nb = 0; nb < 2; ++nb)
-                            acc[mb][nb] =
-                                __builtin_amdgcn_mfma_f32_16x16x4f32(aop[nb][h][j], bop[mb][h][j], acc[mb][nb], 0, 0, 0);
-#pragma unroll
-            for (int mb = 0; mb < 4; ++mb) {
-                bop[mb][0] = bnx[mb][0];
-                bop[mb][1] = bnx[mb][1];
-            }
-        }
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
-            const int X = x0 + 16 * mb + col;
-            if (X >= G) continue;
-            v4f* dst = reinterpret_cast<v4f*>(out + (row * G + X) * C + 4 * grp);
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb) {
-                const v4f a = acc[mb][nb];
-                dst[4 * nb] = v4f{ fmaxf(a.x, 0.f), fmaxf(a.y, 0.f), fmaxf(a.z, 0.f), fmaxf(a.w, 0.f) };
-            }
-        }
-    }
-}
+constexpr int NWB = TAPS * 2 * 64;      // BF16 weights of one 32 -> 32 layer (bf16x8 entries)
+constexpr int kBlock = 256;       // weight preparation
 
 // BF16 operand-ordered weights: wb[(tap * 2 + nb) * 64 + l] holds, as 8 BF16 (rounded to
 // nearest even), W[16 nb + l%16][8 (l/16) + j][tap] for j = 0..7: the A operand of
@@ -458,7 +344,7 @@ __global__ __launch_bounds__(kZ1Threads) void k3c_zconv1_split(int32_t G, int zp
 {
     constexpr int NCELL = ZSY * ZSX;
     static_assert(NCELL <= kZ1Threads && ZY * ZX == (kZ1Threads / 64) * 16, "one slab cell per thread");
-    static_assert((NWB + NW1S) * sizeof(bf16x8) <= NWT * sizeof(float), "layer 1's operands fit after layer 2's");
+    static_assert(NWB + NW1S <= TAPS * 2 * 3 * 64, "layer 1's operands fit after layer 2's");
     __shared__ __attribute__((aligned(16))) bf16x8 s_v[3 * NCELL];
     __shared__ bf16x8 s_w[NW1S];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -531,106 +417,288 @@ __global__ __launch_bounds__(kZ1Threads) void k3c_zconv1_split(int32_t G, int zp
     }
 }
 
-// Layer 4 of the FP32 pass (32 -> 3) as a z-sweep on the vector ALUs: a block owns a column of
-// Z4Y x Z4X cells (one per thread) and zp output planes, and reads each input plane once, as one
-// slab with its one-cell border in LDS.  An input plane p feeds output planes p + 1, p and p - 1
-// (kernel depth index 0, 1, 2), so a thread keeps the partial sums of three output planes; after
-// plane p, output plane p - 1 is complete and written.  The weights are uniform across the block
-// (scalar loads); the next plane's slab is loaded into registers while this one is used.
-constexpr int Z4Y = 8, Z4X = 64;
-constexpr int Z4SY = Z4Y + 2, Z4SX = Z4X + 2;
-constexpr int Z4CS = C + 4;  // floats per slab cell (32 channels + 4 pad)
-constexpr int kZ4Threads = Z4Y * Z4X;
-constexpr int Z4CHUNKS = Z4SY * Z4SX * (C / 4);
-constexpr int Z4CH_PER_THREAD = (Z4CHUNKS + kZ4Threads - 1) / kZ4Threads;
+// Layers 2 and 3 of the FP32 pass, 32 -> 32, on the BF16 matrix instruction with activations and weights as
+// three BF16 values each (split.h), as z-sweeps.  A block owns a column of ZY x ZX cells, zp output planes and
+// 16 of the 32 output channels (the grid's second dimension is the half), so that all 27 taps' weights, 81 KiB,
+// fit in LDS.  It reads each input plane once, as one slab with its one-cell border, split where it enters
+// LDS (so an activation is split about three times in all, not 27); the next plane is loaded into
+// registers while this one is used.  An input plane p feeds output planes p + 1, p and p - 1, whose accumulators
+// are kept for two 16-cell M-blocks per wavefront, the products of the high parts and the small products apart
+// until the end; a tap (dy, dx) of the plane is 36 matrix instructions: three depths, two M-blocks, six products.
+//
+// What bounds it: matrix instructions, 324 per wavefront and plane (16.5 cycles each), and with them the 300 or
+// so vector instructions of the split (3 cycles each, which add up, cnn_rows.h).
+constexpr int NWS = TAPS * 2 * 3 * 64;    // bf16x8 of layers 2 and 3: half, (dy, dx), dz, part
+constexpr int ZROWV = ZSY * ZSX * 4;      // bf16x8 of one part of a slab: 64 bytes a cell
+constexpr int ZSCHUNKS = ZSY * ZSX * (C / 4);
+constexpr int ZSCH_PER_THREAD = (ZSCHUNKS + kZThreads - 1) / kZThreads;
 
-// w4t[(t9 * C + ci) * 9 + d * 3 + o] = W4[o][ci][d * 9 + t9]: for one (dy, dx) the 288 weights
-// of all channels, depths and outputs are contiguous (scalar loads of whole lines)
-__device__ __forceinline__ void wprep4_f32(int k, const float* __restrict__ w, float* __restrict__ w4t)
+// ws[(((nb * 9 + t9) * 3 + dz) * 3 + part) * 64 + l][j]: that part of W[16 nb + l%16][8 (l/16) + j][dz][t9]
+__device__ __forceinline__ void wprep_split(int k, const float* __restrict__ w, bf16x8* __restrict__ ws)
 {
-    const int o = k % 3, d = (k / 3) % 3, ci = (k / 9) % C, t9 = k / (9 * C);
-    w4t[k] = w[(o * C + ci) * TAPS + d * 9 + t9];
+    const int l = k & 63, part = (k >> 6) % 3, dz = (k / 192) % 3, t9 = (k / 576) % 9, nb = k / 5184;
+    bf16x8 v;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        v[j] = split_part(w[((16 * nb + (l & 15)) * C + 8 * (l >> 4) + j) * TAPS + dz * 9 + t9], part);
+    ws[k] = v;
 }
 
-__global__ __launch_bounds__(kZ4Threads) void k3c_zconv4_f32(int32_t G, int zp, const float* __restrict__ in,
-                                                              const float* __restrict__ w,
-                                                              const float* __restrict__ bias, float* __restrict__ disp)
+// One part of a slab in LDS: four 16-byte chunks of eight channels a cell, chunk c of cell i at place
+// c ^ 2 (i / 4 mod 2).  A 16-byte read is served in groups of 16 lanes (see ZCS), here eight consecutive cells at
+// chunk c and eight others at chunk 3 - c; eight consecutive cells take each place of a 256-byte line of four
+// cells twice, i / 4 odd and even, which the exchange puts on chunks c and c ^ 2, and 3 - c has the other
+// parity: no two of the sixteen share a bank.
+__device__ __forceinline__ int slab_slot(int cell, int c)
 {
-    __shared__ __attribute__((aligned(16))) float s_a[Z4SY * Z4SX * Z4CS];
-    const int tid = threadIdx.x;
-    const int tiles_x = (G + Z4X - 1) / Z4X, tiles_y = (G + Z4Y - 1) / Z4Y;
+    return cell * 4 + (c ^ ((cell >> 1) & 2));
+}
+
+__global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k3c_zsplit_f32(
+    int32_t G, int zp, const float* __restrict__ in, const bf16x8* __restrict__ ws, const float* __restrict__ bias,
+    float* __restrict__ out)
+{
+    constexpr int NW = NWS / 2;
+    __shared__ bf16x8 s_w[NW];
+    __shared__ bf16x8 s_slab[3 * ZROWV];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int col = lane & 15, grp = lane >> 4;
+    const int tiles_x = (G + ZX - 1) / ZX, tiles_y = (G + ZY - 1) / ZY;
     const int64_t b = blockIdx.x;
-    const int tx0 = (int)(b % tiles_x) * Z4X, ty0 = (int)((b / tiles_x) % tiles_y) * Z4Y;
+    const int tx0 = (int)(b % tiles_x) * ZX, ty0 = (int)((b / tiles_x) % tiles_y) * ZY;
     const int z0 = (int)(b / ((int64_t)tiles_x * tiles_y)) * zp;
     const int z1 = min(z0 + zp, G);
-    const int64_t GG = (int64_t)G * G, n = GG * G;
-    const int r = tid / Z4X, c = tid % Z4X;
-    const int gy = ty0 + r, gx = tx0 + c;
-    const float b0 = bias[0], b1 = bias[1], b2 = bias[2];
+    const int64_t GG = (int64_t)G * G;
+    const int nb = blockIdx.y;
 
-    v4f pf[Z4CH_PER_THREAD];
+    // plane p of the slab, four channels a load, from clamped positions; what lies outside the grid is zeroed
+    // when it is split into LDS (a thread past the end repeats the last chunk)
+    v4f pf[ZSCH_PER_THREAD];
     auto fetch = [&](int p) {
+        int t = tid;
+        asm volatile("" : "+v"(t));  // positions are formed per plane, not held in registers
+        const float* plane = in + (int64_t)min(max(p, 0), G - 1) * GG * C;
 #pragma unroll
-        for (int k = 0; k < Z4CH_PER_THREAD; ++k) {
-            const int e = tid + k * kZ4Threads;
-            v4f v{ 0.f, 0.f, 0.f, 0.f };
-            if (e < Z4CHUNKS) {
-                const int cell = e / (C / 4), part = e % (C / 4);
-                const int y = ty0 + cell / Z4SX - 1, x = tx0 + cell % Z4SX - 1;
-                if (p >= 0 && p < G && y >= 0 && y < G && x >= 0 && x < G)
-                    v = *reinterpret_cast<const v4f*>(in + ((int64_t)p * GG + (int64_t)y * G + x) * C + 4 * part);
+        for (int k = 0; k < ZSCH_PER_THREAD; ++k) {
+            const int e = min(t + k * kZThreads, ZSCHUNKS - 1), cell = e >> 3;
+            const int gy = min(max(ty0 + cell / ZSX - 1, 0), G - 1), gx = min(max(tx0 + cell % ZSX - 1, 0), G - 1);
+            pf[k] = *reinterpret_cast<const v4f*>(plane + (unsigned)((gy * G + gx) * C + 4 * (e & 7)));
+        }
+    };
+    auto stash = [&](int p) {
+        int t = tid;
+        asm volatile("" : "+v"(t));
+        const bool pin = p >= 0 && p < G;
+#pragma unroll
+        for (int k = 0; k < ZSCH_PER_THREAD; ++k) {
+            const int e = min(t + k * kZThreads, ZSCHUNKS - 1), cell = e >> 3;
+            const int gy = ty0 + cell / ZSX - 1, gx = tx0 + cell % ZSX - 1;
+            const bool on = pin && gy >= 0 && gy < G && gx >= 0 && gx < G;
+            const v4f x = on ? pf[k] : v4f{ 0.f, 0.f, 0.f, 0.f };
+            u32x2 h, m, l;
+            uint32_t ph, pm, pl;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                split_pair(x[2 * j], x[2 * j + 1], ph, pm, pl);
+                h[j] = ph;
+                m[j] = pm;
+                l[j] = pl;
             }
-            pf[k] = v;
+            u32x2* to = reinterpret_cast<u32x2*>(s_slab + slab_slot(cell, (e & 7) >> 1)) + (e & 1);
+            to[0] = h;
+            to[2 * ZROWV] = m;
+            to[4 * ZROWV] = l;
         }
     };
-    auto stash = [&]() {
-#pragma unroll
-        for (int k = 0; k < Z4CH_PER_THREAD; ++k) {
-            const int e = tid + k * kZ4Threads;
-            if (e < Z4CHUNKS) *reinterpret_cast<v4f*>(s_a + (e / (C / 4)) * Z4CS + 4 * (e % (C / 4))) = pf[k];
-        }
-    };
-    // acc[d][o]: output plane p + 1 - d, component o
-    float acc[3][CIO];
+    fetch(z0 - 1);
+    for (int k = tid; k < NW; k += kZThreads) s_w[k] = ws[nb * NW + k];
+    stash(z0 - 1);
+    __syncthreads();
+
+    const v4f zero = v4f{ 0.f, 0.f, 0.f, 0.f };
+    const v4f bl = *reinterpret_cast<const v4f*>(bias + 16 * nb + 4 * grp);  // of the lane's output channels
+    v4f hi[3][2], lo[3][2];  // [dz][M-block]: output planes p + 1 - dz
 #pragma unroll
     for (int d = 0; d < 3; ++d)
 #pragma unroll
-        for (int o = 0; o < CIO; ++o) acc[d][o] = 0.f;
-    fetch(z0 - 1);
+        for (int h = 0; h < 2; ++h) {
+            hi[d][h] = bl;
+            lo[d][h] = zero;
+        }
+    // wavefront: cells (ty0 + wave, tx0 + 16 h + col), h = 0, 1
     for (int p = z0 - 1; p <= z1; ++p) {
-        __syncthreads();  // every thread is done with the previous plane's slab
-        stash();
-        __syncthreads();
-        if (p + 1 <= z1) fetch(p + 1);  // lands while this plane is used
-#pragma unroll 1
+        if (p < z1) fetch(p + 1);  // lands while this plane is used
+        int ln = lane;
+        asm volatile("" : "+v"(ln));  // the addresses are formed per plane, not held in registers
+        const int cell0 = wave * ZSX + (ln & 15), q = ln >> 4;
+        bf16x8 w[2][3][3], x[2][2][3];
+        auto load = [&](int t9) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+#pragma unroll
+                for (int part = 0; part < 3; ++part) w[t9 & 1][d][part] = s_w[((t9 * 3 + d) * 3 + part) * 64 + ln];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int part = 0; part < 3; ++part)
+                    x[t9 & 1][h][part] = s_slab[part * ZROWV + slab_slot(cell0 + 16 * h + (t9 / 3) * ZSX + t9 % 3, q)];
+        };
+        load(0);
+#pragma unroll
         for (int t9 = 0; t9 < 9; ++t9) {
-            const int dy = t9 / 3, dx = t9 % 3;
-            const v4f* a4 = reinterpret_cast<const v4f*>(s_a + ((r + dy) * Z4SX + c + dx) * Z4CS);
-#pragma unroll 2
-            for (int q = 0; q < C / 4; ++q) {
-                const v4f a = a4[q];
+            __builtin_amdgcn_sched_barrier(0);
+            if (t9 + 1 < 9) load(t9 + 1);
+            __builtin_amdgcn_sched_barrier(0);  // the next tap's reads are issued before this tap's products
+            constexpr int wp[6] = { 2, 0, 0, 1, 1, 0 }, xp[6] = { 0, 0, 2, 1, 0, 1 };
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int ci = 4 * q + j;
+            for (int k = 0; k < 6; ++k)
 #pragma unroll
-                    for (int d = 0; d < 3; ++d)
+                for (int d = 0; d < 3; ++d)
 #pragma unroll
-                        for (int o = 0; o < CIO; ++o) acc[d][o] += w[(t9 * C + ci) * 9 + d * 3 + o] * a[j];
-                }
+                    for (int h = 0; h < 2; ++h) {
+                        v4f& acc = k == 1 ? hi[d][h] : lo[d][h];
+                        acc = mfma_bf16(w[t9 & 1][d][wp[k]], x[t9 & 1][h][xp[k]], acc);
+                    }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // output plane p - 1 is complete
+        const int zo = p - 1, gy = ty0 + wave;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int gx = tx0 + 16 * h + col;
+            if (zo >= z0 && gy < G && gx < G) {
+                v4f v = hi[2][h] + lo[2][h];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.f);
+                *reinterpret_cast<v4f*>(out + ((int64_t)zo * GG + (int64_t)gy * G + gx) * C + 16 * nb + 4 * grp) = v;
             }
-        }
-        const int zo = p - 1;  // complete now: its last input plane was p
-        if (zo >= z0 && zo < z1 && gy < G && gx < G) {
-            const int64_t cell = (int64_t)zo * GG + (int64_t)gy * G + gx;
-            disp[cell] = acc[2][0] + b0;
-            disp[n + cell] = acc[2][1] + b1;
-            disp[2 * n + cell] = acc[2][2] + b2;
-        }
 #pragma unroll
-        for (int o = 0; o < CIO; ++o) {
-            acc[2][o] = acc[1][o];
-            acc[1][o] = acc[0][o];
-            acc[0][o] = 0.f;
+            for (int d = 2; d > 0; --d) {
+                hi[d][h] = hi[d - 1][h];
+                lo[d][h] = lo[d - 1][h];
+            }
+            hi[0][h] = bl;
+            lo[0][h] = zero;
+        }
+        if (p < z1) {
+            __syncthreads();  // every wavefront is done with this plane's slab
+            stash(p + 1);
+            __syncthreads();
+        }
+    }
+}
+
+// Layer 4 of the FP32 pass (32 -> 3) as a z-sweep on the FP32 matrix instruction (a product of one weight and
+// one activation is rounded once, which the split form does not do).  Rows 4 o + dz of one A block are output
+// component o and kernel depth dz, so a tap (dy, dx) of an input plane is eight instructions of K = 4 per 16 cells
+// for all three output planes it feeds, and a lane's result holds, for component l / 16, the three depths:
+// the sums of the unfinished planes move down one element per plane.  The rest is k3c_zsplit_f32's.  On the
+// vector ALUs, a cell per thread and nine sums each, the layer took 284 us at G = 128 and 77 us at G = 9.
+constexpr int NW4F = 9 * 2 * 64;              // v4f of layer 4's weights: (dy, dx), half of the channels
+constexpr int Z4LINES = ZSY * ZSX / 2;        // 256-byte lines of a slab, two cells each
+static_assert(ZSX % 2 == 0, "a slab row starts a line");
+
+// The chunk (four channels) that lane group q reads as half h of its eight: 2q and 2q + 1, exchanged for q >= 2,
+// and chunk c's place in a slab: in a line k of two cells, cell p of it at (8 p + c + 2 k) mod 16.  Eight
+// consecutive cells at one chunk and eight at another of the other parity (a 16-lane group of a 16-byte read,
+// see ZCS) then fall in distinct banks.
+__host__ __device__ constexpr int chunk4(int q, int h)
+{
+    return 2 * q + (h ^ (q >> 1));
+}
+__device__ __forceinline__ int slab4_slot(int cell, int c)
+{
+    const int k = cell >> 1;
+    return k * 16 + ((8 * (cell & 1) + c + 2 * k) & 15);
+}
+
+// w4f[(t9 * 2 + h) * 64 + l][j] = W4[o][4 chunk4(l/16, h) + j][dz][t9] with l%16 = 4 o + dz (zero for o = 3, dz = 3)
+__device__ __forceinline__ void wprep4_f32(int k, const float* __restrict__ w, v4f* __restrict__ w4f)
+{
+    const int l = k & 63, h = (k >> 6) & 1, t9 = k >> 7, o = (l & 15) >> 2, dz = l & 3;
+    v4f v;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        v[j] = o < CIO && dz < 3 ? w[(o * C + 4 * chunk4(l >> 4, h) + j) * TAPS + dz * 9 + t9] : 0.f;
+    w4f[k] = v;
+}
+
+__global__ __launch_bounds__(kZThreads) void k3c_zconv4_f32(int32_t G, int zp, const float* __restrict__ in,
+                                                             const v4f* __restrict__ w4f,
+                                                             const float* __restrict__ bias, float* __restrict__ disp)
+{
+    __shared__ v4f s_w[NW4F];
+    __shared__ v4f s_slab[Z4LINES * 16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int col = lane & 15, grp = lane >> 4;
+    const int tiles_x = (G + ZX - 1) / ZX, tiles_y = (G + ZY - 1) / ZY;
+    const int64_t b = blockIdx.x;
+    const int tx0 = (int)(b % tiles_x) * ZX, ty0 = (int)((b / tiles_x) % tiles_y) * ZY;
+    const int z0 = (int)(b / ((int64_t)tiles_x * tiles_y)) * zp;
+    const int z1 = min(z0 + zp, G);
+    const int64_t GG = (int64_t)G * G;
+
+    v4f pf[ZSCH_PER_THREAD];
+    auto fetch = [&](int p) {
+        const float* plane = in + (int64_t)min(max(p, 0), G - 1) * GG * C;
+#pragma unroll
+        for (int k = 0; k < ZSCH_PER_THREAD; ++k) {
+            const int e = min(tid + k * kZThreads, ZSCHUNKS - 1), cell = e >> 3;
+            const int gy = min(max(ty0 + cell / ZSX - 1, 0), G - 1), gx = min(max(tx0 + cell % ZSX - 1, 0), G - 1);
+            pf[k] = *reinterpret_cast<const v4f*>(plane + (unsigned)((gy * G + gx) * C + 4 * (e & 7)));
+        }
+    };
+    auto stash = [&](int p) {
+        const bool pin = p >= 0 && p < G;
+#pragma unroll
+        for (int k = 0; k < ZSCH_PER_THREAD; ++k) {
+            const int e = min(tid + k * kZThreads, ZSCHUNKS - 1), cell = e >> 3;
+            const int gy = ty0 + cell / ZSX - 1, gx = tx0 + cell % ZSX - 1;
+            const bool on = pin && gy >= 0 && gy < G && gx >= 0 && gx < G;
+            s_slab[slab4_slot(cell, e & 7)] = on ? pf[k] : v4f{ 0.f, 0.f, 0.f, 0.f };
+        }
+    };
+    fetch(z0 - 1);
+    for (int k = tid; k < NW4F; k += kZThreads) s_w[k] = w4f[k];
+    stash(z0 - 1);
+    __syncthreads();
+    const float bo = grp < CIO ? bias[grp] : 0.f;
+    v4f acc[2];  // per M-block: element dz is output plane p + 1 - dz
+    acc[0] = acc[1] = v4f{ 0.f, 0.f, 0.f, 0.f };
+    for (int p = z0 - 1; p <= z1; ++p) {
+        if (p < z1) fetch(p + 1);  // lands while this plane is used
+        const int cell0 = wave * ZSX + col;
+#pragma unroll
+        for (int t9 = 0; t9 < 9; ++t9) {
+            v4f w[2], x[2][2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                w[h] = s_w[(t9 * 2 + h) * 64 + lane];
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+                    x[m][h] = s_slab[slab4_slot(cell0 + 16 * m + (t9 / 3) * ZSX + t9 % 3, chunk4(grp, h))];
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int m = 0; m < 2; ++m)
+                        acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[h][j], x[m][h][j], acc[m], 0, 0, 0);
+        }
+        // output plane p - 1 is complete
+        const int zo = p - 1, gy = ty0 + wave;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int gx = tx0 + 16 * m + col;
+            if (zo >= z0 && gy < G && gx < G && grp < CIO)
+                disp[grp * GG * G + (int64_t)zo * GG + (int64_t)gy * G + gx] = acc[m][2] + bo;
+            acc[m] = v4f{ 0.f, acc[m][0], acc[m][1], 0.f };
+        }
+        if (p < z1) {
+            __syncthreads();  // every wavefront is done with this plane's slab
+            stash(p + 1);
+            __syncthreads();
         }
     }
 }
@@ -650,14 +718,14 @@ __global__ void k3c_prep_bf16(const float* __restrict__ w1, const float* __restr
 constexpr int kPrepBf16 = 2 * NWB + NW1S + TAPS * 64;
 
 __global__ void k3c_prep_f32(const float* __restrict__ w2, const float* __restrict__ w3, const float* __restrict__ w4,
-                             float* __restrict__ wt2, float* __restrict__ wt3, float* __restrict__ w4t)
+                             bf16x8* __restrict__ ws2, bf16x8* __restrict__ ws3, v4f* __restrict__ w4f)
 {
     int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < NWT) return wprep(k, w2, wt2);
-    if ((k -= NWT) < NWT) return wprep(k, w3, wt3);
-    if ((k -= NWT) < TAPS * C * CIO) wprep4_f32(k, w4, w4t);
+    if (k < NWS) return wprep_split(k, w2, ws2);
+    if ((k -= NWS) < NWS) return wprep_split(k, w3, ws3);
+    if ((k -= NWS) < NW4F) wprep4_f32(k, w4, w4f);
 }
-constexpr int kPrepF32 = 2 * NWT + TAPS * C * CIO;
+constexpr int kPrepF32 = 2 * NWS + NW4F;
 
 // Planes per block of a z-sweep over `tiles` columns, `slots` blocks running at once: the length that makes
 // the busiest place's planes fewest, a block costing about three planes besides its own (its weights and the two
@@ -687,7 +755,7 @@ inline int z_planes(int G, int64_t tiles, int slots)
 size_t cnn3_workspace_bytes(int32_t G)
 {
     const size_t cells = (size_t)G * G * G;
-    return 2 * cells * C * sizeof(float) + 2 * (size_t)NWT * sizeof(float) + (size_t)TAPS * C * CIO * sizeof(float);
+    return 2 * cells * C * sizeof(float) + (2 * (size_t)NWS + (size_t)NW4F) * sizeof(bf16x8);
 }
 
 void run_predict3(cnnsns_mesh3_s& m, const float* vel, const cnnsns_cnn& w, int32_t precision, float* disp,
@@ -705,14 +773,12 @@ void run_predict3(cnnsns_mesh3_s& m, const float* vel, const cnnsns_cnn& w, int3
     if (zblocks > (int64_t)UINT32_MAX) fail(CNNSNS_EINVAL, "predict3d: overlay too large");
     float* act0 = static_cast<float*>(m.ws.ptr);
     float* act1 = act0 + cells * C;
-    float* wt2 = act1 + cells * C;
-    float* wt3 = wt2 + NWT;
+    bf16x8* wb2 = reinterpret_cast<bf16x8*>(act1 + cells * C);
+    bf16x8* wb3 = wb2 + NWS;
     if (precision == CNNSNS_BF16) {
         bf16* b0 = reinterpret_cast<bf16*>(act0);
         bf16* b1 = reinterpret_cast<bf16*>(act1);
-        bf16x8* wb2 = reinterpret_cast<bf16x8*>(wt2);
-        bf16x8* wb3 = reinterpret_cast<bf16x8*>(wt3);
-        bf16x8* wb1 = wb2 + NWB;  // after layer 2's operands in their 108 KiB region, and layer 4's after layer 3's
+        bf16x8* wb1 = wb2 + NWB;  // after layer 2's operands in their region, and layer 4's after layer 3's
         bf16x8* wb4 = wb3 + NWB;
         k3c_prep_bf16<<<(kPrepBf16 + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[0], w.w[1], w.w[2], w.w[3], wb1, wb2,
                                                                               wb3, wb4);
@@ -721,16 +787,14 @@ void run_predict3(cnnsns_mesh3_s& m, const float* vel, const cnnsns_cnn& w, int3
         k3c_zsweep_bf16<2><<<(unsigned)zblocks, kZThreads, 0, stream>>>(G, zp, b1, wb3, w.b[2], b0, nullptr);
         k3c_zsweep_bf16<1><<<(unsigned)zblocks, kZThreads, 0, stream>>>(G, zp, b0, wb4, w.b[3], nullptr, disp);
     } else {
-        float* w4t = wt3 + NWT;
-        k3c_prep_f32<<<(kPrepF32 + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[1], w.w[2], w.w[3], wt2, wt3, w4t);
+        v4f* w4f = reinterpret_cast<v4f*>(wb3 + NWS);
+        k3c_prep_f32<<<(kPrepF32 + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[1], w.w[2], w.w[3], wb2, wb3, w4f);
         k3c_zconv1<float><<<(unsigned)zblocks, kZ1Threads, 0, stream>>>(G, zp, vel, w.w[0], w.b[0], act0);
-        k3c_conv32<<<grid, kWaves32 * 64, 0, stream>>>(G, act0, wt2, w.b[1], act1);
-        k3c_conv32<<<grid, kWaves32 * 64, 0, stream>>>(G, act1, wt3, w.b[2], act0);
-        const int64_t z4tiles = (int64_t)((G + Z4X - 1) / Z4X) * ((G + Z4Y - 1) / Z4Y);
-        const int z4p = z_planes(G, z4tiles, (int)grid);
-        const int64_t z4blocks = z4tiles * ((G + z4p - 1) / z4p);
-        if (z4blocks > (int64_t)UINT32_MAX) fail(CNNSNS_EINVAL, "predict3d: overlay too large");
-        k3c_zconv4_f32<<<(unsigned)z4blocks, kZ4Threads, 0, stream>>>(G, z4p, act0, w4t, w.b[3], disp);
+        const int zp2 = z_planes(G, 2 * ztiles, (int)grid);
+        const dim3 g2((unsigned)(ztiles * ((G + zp2 - 1) / zp2)), 2);
+        k3c_zsplit_f32<<<g2, kZThreads, 0, stream>>>(G, zp2, act0, wb2, w.b[1], act1);
+        k3c_zsplit_f32<<<g2, kZThreads, 0, stream>>>(G, zp2, act1, wb3, w.b[2], act0);
+        k3c_zconv4_f32<<<(unsigned)zblocks, kZThreads, 0, stream>>>(G, zp, act0, w4f, w.b[3], disp);
     }
     hip_check(hipGetLastError(), "predict3d launch");
     workspace_used(m.ws, stream);
