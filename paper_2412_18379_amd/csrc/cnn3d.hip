@@ -472,29 +472,30 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2)
     const int nb = blockIdx.y;
 
     // plane p of the slab, four channels a load, from clamped positions; what lies outside the grid is zeroed
-    // when it is split into LDS (a thread past the end repeats the last chunk)
+    // when it is split into LDS (a thread past the end repeats the last chunk).  A chunk's place in the
+    // plane is the same in every plane: formed once (per plane it was half of the sweep's vector instructions).
     v4f pf[ZSCH_PER_THREAD];
+    unsigned at[ZSCH_PER_THREAD];
+    u32x2* to[ZSCH_PER_THREAD];
+    bool on[ZSCH_PER_THREAD];
+#pragma unroll
+    for (int k = 0; k < ZSCH_PER_THREAD; ++k) {
+        const int e = min(tid + k * kZThreads, ZSCHUNKS - 1), cell = e >> 3;
+        const int gy = ty0 + cell / ZSX - 1, gx = tx0 + cell % ZSX - 1;
+        on[k] = gy >= 0 && gy < G && gx >= 0 && gx < G;
+        at[k] = (min(max(gy, 0), G - 1) * G + min(max(gx, 0), G - 1)) * C + 4 * (e & 7);
+        to[k] = reinterpret_cast<u32x2*>(s_slab + slab_slot(cell, (e & 7) >> 1)) + (e & 1);
+    }
     auto fetch = [&](int p) {
-        int t = tid;
-        asm volatile("" : "+v"(t));  // positions are formed per plane, not held in registers
         const float* plane = in + (int64_t)min(max(p, 0), G - 1) * GG * C;
 #pragma unroll
-        for (int k = 0; k < ZSCH_PER_THREAD; ++k) {
-            const int e = min(t + k * kZThreads, ZSCHUNKS - 1), cell = e >> 3;
-            const int gy = min(max(ty0 + cell / ZSX - 1, 0), G - 1), gx = min(max(tx0 + cell % ZSX - 1, 0), G - 1);
-            pf[k] = *reinterpret_cast<const v4f*>(plane + (unsigned)((gy * G + gx) * C + 4 * (e & 7)));
-        }
+        for (int k = 0; k < ZSCH_PER_THREAD; ++k) pf[k] = *reinterpret_cast<const v4f*>(plane + at[k]);
     };
     auto stash = [&](int p) {
-        int t = tid;
-        asm volatile("" : "+v"(t));
         const bool pin = p >= 0 && p < G;
 #pragma unroll
         for (int k = 0; k < ZSCH_PER_THREAD; ++k) {
-            const int e = min(t + k * kZThreads, ZSCHUNKS - 1), cell = e >> 3;
-            const int gy = ty0 + cell / ZSX - 1, gx = tx0 + cell % ZSX - 1;
-            const bool on = pin && gy >= 0 && gy < G && gx >= 0 && gx < G;
-            const v4f x = on ? pf[k] : v4f{ 0.f, 0.f, 0.f, 0.f };
+            const v4f x = on[k] && pin ? pf[k] : v4f{ 0.f, 0.f, 0.f, 0.f };
             u32x2 h, m, l;
             uint32_t ph, pm, pl;
 #pragma unroll
@@ -504,10 +505,9 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2)
                 m[j] = pm;
                 l[j] = pl;
             }
-            u32x2* to = reinterpret_cast<u32x2*>(s_slab + slab_slot(cell, (e & 7) >> 1)) + (e & 1);
-            to[0] = h;
-            to[2 * ZROWV] = m;
-            to[4 * ZROWV] = l;
+            to[k][0] = h;
+            to[k][2 * ZROWV] = m;
+            to[k][4 * ZROWV] = l;
         }
     };
     fetch(z0 - 1);
@@ -639,24 +639,26 @@ __global__ __launch_bounds__(kZThreads) void k3c_zconv4_f32(int32_t G, int zp, c
     const int64_t GG = (int64_t)G * G;
 
     v4f pf[ZSCH_PER_THREAD];
+    unsigned at[ZSCH_PER_THREAD];
+    int to[ZSCH_PER_THREAD];
+    bool on[ZSCH_PER_THREAD];
+#pragma unroll
+    for (int k = 0; k < ZSCH_PER_THREAD; ++k) {
+        const int e = min(tid + k * kZThreads, ZSCHUNKS - 1), cell = e >> 3;
+        const int gy = ty0 + cell / ZSX - 1, gx = tx0 + cell % ZSX - 1;
+        on[k] = gy >= 0 && gy < G && gx >= 0 && gx < G;
+        at[k] = (min(max(gy, 0), G - 1) * G + min(max(gx, 0), G - 1)) * C + 4 * (e & 7);
+        to[k] = slab4_slot(cell, e & 7);
+    }
     auto fetch = [&](int p) {
         const float* plane = in + (int64_t)min(max(p, 0), G - 1) * GG * C;
 #pragma unroll
-        for (int k = 0; k < ZSCH_PER_THREAD; ++k) {
-            const int e = min(tid + k * kZThreads, ZSCHUNKS - 1), cell = e >> 3;
-            const int gy = min(max(ty0 + cell / ZSX - 1, 0), G - 1), gx = min(max(tx0 + cell % ZSX - 1, 0), G - 1);
-            pf[k] = *reinterpret_cast<const v4f*>(plane + (unsigned)((gy * G + gx) * C + 4 * (e & 7)));
-        }
+        for (int k = 0; k < ZSCH_PER_THREAD; ++k) pf[k] = *reinterpret_cast<const v4f*>(plane + at[k]);
     };
     auto stash = [&](int p) {
         const bool pin = p >= 0 && p < G;
 #pragma unroll
-        for (int k = 0; k < ZSCH_PER_THREAD; ++k) {
-            const int e = min(tid + k * kZThreads, ZSCHUNKS - 1), cell = e >> 3;
-            const int gy = ty0 + cell / ZSX - 1, gx = tx0 + cell % ZSX - 1;
-            const bool on = pin && gy >= 0 && gy < G && gx >= 0 && gx < G;
-            s_slab[slab4_slot(cell, e & 7)] = on ? pf[k] : v4f{ 0.f, 0.f, 0.f, 0.f };
-        }
+        for (int k = 0; k < ZSCH_PER_THREAD; ++k) s_slab[to[k]] = on[k] && pin ? pf[k] : v4f{ 0.f, 0.f, 0.f, 0.f };
     };
     fetch(z0 - 1);
     for (int k = tid; k < NW4F; k += kZThreads) s_w[k] = w4f[k];
