@@ -30,11 +30,12 @@
 #include <hipcub/hipcub.hpp>
 
 #include "common.h"
+#include "split.h"
 
 namespace cnnsns {
 namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kW = 9, kR = 4, kNA = kW * kW;  // window side, radius, classes
 constexpr int kC = 16;                         // conv channels
@@ -281,89 +282,185 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
     }
 }
 
-// C[m][n] = act(bias[n] + sum_k A[m][k] W[n][k]) for m < M, n < N (W in [out][in] layout); K a multiple of 16,
-// rows of A and W 16-byte aligned.  128 x 128 output tiles, four wavefronts of 64 x 64 each (4 x 4 blocks of
-// v_mfma_f32_16x16x4f32, so each operand read from LDS feeds four instructions); the next 16-wide K slice
-// is loaded into registers while this one's products issue.
-constexpr int kDT = 128;  // dense tile side
-template <bool RELU>
-__global__ __launch_bounds__(kBlock) void k_dense_f32(int M, int N, int K, const float* __restrict__ A, int lda,
-                                                      const float* __restrict__ Wt, const float* __restrict__ bias,
-                                                      float* __restrict__ Cm, int ldc)
+// The wide fully connected layers, C[m][n] = act(bias[n] + sum_k A[m][k] W[n][k]) for m < M, on the BF16 matrix
+// instruction with both operands as three BF16 values (split.h).  A block takes BM particles x BN outputs; a
+// wavefront MB x NB blocks of 16 x 16 (rows = outputs, columns = particles, so a lane ends with four consecutive
+// outputs of a particle), the products of the high parts and the small ones in accumulators of their
+// own.  K goes in slices of 32, double-buffered in LDS: the weights' operands are copied straight into LDS as
+// prepared (k_cls_prep), the activations are loaded into registers, split and written after the slice's products.
+//
+// What bounds it: matrix instructions, 96 per wavefront and slice (16.5 cycles each) at 128 x 256.  65,536
+// particles: 512 -> 512 took 0.36 ms on the FP32 instruction in 128 x 128 tiles.
+constexpr int kDenseThreads = 512;
+
+// Operand-ordered split weights of a layer with N (padded to 16) outputs and K inputs:
+// ws[((ks * (N / 16) + n16) * 3 + part) * 64 + l][j] = that part of W[16 n16 + l%16][32 ks + 8 (l/16) + j].
+__device__ __forceinline__ void dense_prep(int k, int N, int K, int n_real, const float* __restrict__ w,
+                                           bf16x8* __restrict__ ws)
 {
-    __shared__ float sA[2][kDT][17], sB[2][kDT][17];
-    const int m0 = blockIdx.x * kDT, n0 = blockIdx.y * kDT;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
-    const int row = lane & 15, kq = lane >> 4;
-    // the two float4 of each operand tile this thread stages: rows tid / 4 and tid / 4 + 64
-    const int sr = tid >> 2, sc = (tid & 3) * 4;
-    v4f acc[4][4];
+    const int l = k & 63, part = (k >> 6) % 3, blk = k / 192, n16 = blk % (N / 16), ks = blk / (N / 16);
+    const int n = 16 * n16 + (l & 15), k0 = 32 * ks + 8 * (l >> 4);
+    bf16x8 v;
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int j = 0; j < 8; ++j) v[j] = split_part(n < n_real ? w[(int64_t)n * K + k0 + j] : 0.f, part);
+    ws[k] = v;
+}
+constexpr int kNL = 96;                                  // the 81 logits padded to six blocks
+constexpr int kD1 = kH1 / 16 * (kH1 / 32) * 192;         // bf16x8 of the three layers
+constexpr int kD2 = kH2 / 16 * (kNZ / 32) * 192;
+constexpr int kD3 = kNL / 16 * (kH2 / 32) * 192;
+
+__global__ void k_cls_prep(const float* __restrict__ w3, const float* __restrict__ w4, const float* __restrict__ w5,
+                           bf16x8* __restrict__ ws)
+{
+    int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < kD1) return dense_prep(k, kH1, kH1, kH1, w3, ws);
+    if ((k -= kD1) < kD2) return dense_prep(k, kH2, kNZ, kH2, w4, ws + kD1);
+    if ((k -= kD2) < kD3) dense_prep(k, kNL, kH2, kNA, w5, ws + kD1 + kD2);
+}
+
+// One part of BM rows of 32 inputs in LDS: four 16-byte chunks of eight a row, chunk c of row r at place
+// c ^ 2 (r / 4 mod 2).  The LDS serves a 16-byte read in groups of 16 lanes over 64 four-byte banks, a group
+// joining lanes 0-7 with 56-63 (8-15 with 48-55, ...): here eight consecutive rows at chunk c and the next eight
+// at chunk 3 - c.  Eight rows take each place of a 256-byte line of four rows twice, r / 4 odd and even, which
+// the exchange puts on chunks c and c ^ 2, and 3 - c has the other parity: sixteen distinct banks.
+__device__ __forceinline__ int dense_slot(int r, int c)
+{
+    return r * 4 + (c ^ ((r >> 1) & 2));
+}
+
+// N outputs, of which n_real exist (rows of C hold ldc; with VEC all exist and a lane's four are stored at once)
+template <int MB, int NB, int WM, int WN, bool RELU, bool VEC>
+__global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_dense_split(
+    int M, int N, int n_real, int K, const float* __restrict__ A, int lda, const bf16x8* __restrict__ ws,
+    const float* __restrict__ bias, float* __restrict__ Cm, int ldc)
+{
+    static_assert(WM * WN * 64 == kDenseThreads, "eight wavefronts");
+    constexpr int BM = 16 * MB * WM, BN = 16 * NB * WN, NF = BN / 16 * 3;  // weight operands of a slice
+    constexpr int PER = BM * 8 / kDenseThreads;
+    static_assert(BM * 8 % kDenseThreads == 0, "whole rounds of activation loads");
+    __shared__ bf16x8 s_w[2][NF * 64];
+    __shared__ bf16x8 s_x[2][3 * BM * 4];
+    const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
+    const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
+
+    // weights of slice ks straight into LDS, one operand (64 lanes x 16 bytes) a wavefront instruction
+    auto load_w = [&](int ks) {
+        const bf16x8* src = ws + ((int64_t)ks * (N / 16) + n0 / 16) * 192 + lane;
+        for (int f = wave; f < NF; f += 8)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + f * 64),
+                                             (__attribute__((address_space(3))) void*)(s_w[ks & 1] + f * 64), 16, 0, 0);
+    };
+    v4f pa[PER];
+    auto fetch = [&](int ks) {
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = v4f{ 0.f, 0.f, 0.f, 0.f };
-    auto fetch = [&](int k0, v4f (&va)[2], v4f (&vb)[2]) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int r = sr + 64 * h;
-            va[h] = m0 + r < M ? *reinterpret_cast<const v4f*>(A + (int64_t)(m0 + r) * lda + k0 + sc)
-                               : v4f{ 0.f, 0.f, 0.f, 0.f };
-            vb[h] = n0 + r < N ? *reinterpret_cast<const v4f*>(Wt + (int64_t)(n0 + r) * K + k0 + sc)
-                               : v4f{ 0.f, 0.f, 0.f, 0.f };
+        for (int h = 0; h < PER; ++h) {
+            const int e = tid + h * kDenseThreads, r = min(m0 + (e >> 3), M - 1);  // rows past M: not stored
+            pa[h] = *reinterpret_cast<const v4f*>(A + (int64_t)r * lda + 32 * ks + 4 * (e & 7));
         }
     };
-    auto stash = [&](int buf, const v4f (&va)[2], const v4f (&vb)[2]) {
+    auto stash = [&](int ks) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < PER; ++h) {
+            const int e = tid + h * kDenseThreads;
+            u32x2 p[3];
+            uint32_t a, b, c;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                sA[buf][sr + 64 * h][sc + e] = va[h][e];
-                sB[buf][sr + 64 * h][sc + e] = vb[h][e];
+            for (int j = 0; j < 2; ++j) {
+                split_pair(pa[h][2 * j], pa[h][2 * j + 1], a, b, c);
+                p[0][j] = a;
+                p[1][j] = b;
+                p[2][j] = c;
             }
-    };
-    v4f va[2], vb[2];
-    fetch(0, va, vb);
-    stash(0, va, vb);
-    __syncthreads();
-    int buf = 0;
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        const bool more = k0 + 16 < K;
-        if (more) fetch(k0 + 16, va, vb);  // lands while this slice's products issue
+            u32x2* to = reinterpret_cast<u32x2*>(s_x[ks & 1] + dense_slot(e >> 3, (e & 7) >> 1)) + (e & 1);
 #pragma unroll
-        for (int kk = 0; kk < 16; kk += 4) {
-            float a[4], b[4];
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                a[x] = sA[buf][wm + 16 * x + row][kk + kq];
-                b[x] = sB[buf][wn + 16 * x + row][kk + kq];
-            }
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-#pragma unroll
-                for (int y = 0; y < 4; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[x], b[y], acc[x][y], 0, 0, 0);
+            for (int part = 0; part < 3; ++part) to[part * BM * 8] = p[part];
         }
-        if (more) stash(buf ^ 1, va, vb);
-        __syncthreads();
-        buf ^= 1;
+    };
+    v4f hi[MB][NB], lo[MB][NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        v4f b;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int n = n0 + 16 * (wn * NB + nb) + 4 * q + r;
+            b[r] = VEC || n < n_real ? bias[n] : 0.f;
+        }
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            hi[mb][nb] = b;
+            lo[mb][nb] = v4f{ 0.f, 0.f, 0.f, 0.f };
+        }
     }
-    // lane holds rows 4 kq + e of column `row` of each 16 x 16 block
+    load_w(0);
+    fetch(0);
+    stash(0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the weights have arrived
+    __syncthreads();
+    const int slices = K / 32;
+    for (int ks = 0; ks < slices; ++ks) {
+        if (ks + 1 < slices) {  // lands while this slice's products issue
+            load_w(ks + 1);
+            fetch(ks + 1);
+        }
+        const bf16x8* sw = s_w[ks & 1] + wn * NB * 192 + lane;
+        const bf16x8* sx = s_x[ks & 1];
+        bf16x8 w[NB][3], x[MB][3];
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+        for (int part = 0; part < 3; ++part) {
 #pragma unroll
-        for (int y = 0; y < 4; ++y) {
-            const int n = n0 + wn + 16 * y + row;
-            if (n >= N) continue;
-            const float bn = bias[n];
+            for (int nb = 0; nb < NB; ++nb) w[nb][part] = sw[(nb * 3 + part) * 64];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int m = m0 + wm + 16 * x + 4 * kq + e;
-                if (m >= M) continue;
-                float v = acc[x][y][e] + bn;
-                if (RELU) v = fmaxf(v, 0.f);
-                Cm[(int64_t)m * ldc + n] = v;
+            for (int mb = 0; mb < MB; ++mb) x[mb][part] = sx[part * BM * 4 + dense_slot(16 * (wm * MB + mb) + i, q)];
+        }
+        constexpr int wp[6] = { 0, 0, 1, 1, 0, 2 }, xp[6] = { 0, 1, 0, 1, 2, 0 };
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    v4f& acc = k == 0 ? hi[mb][nb] : lo[mb][nb];
+                    acc = mfma_bf16(w[nb][wp[k]], x[mb][xp[k]], acc);
+                }
+        if (ks + 1 < slices) stash(ks + 1);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+        const int m = m0 + 16 * (wm * MB + mb) + i;
+        if (m >= M) continue;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int n = n0 + 16 * (wn * NB + nb) + 4 * q;
+            v4f v = hi[mb][nb] + lo[mb][nb];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = RELU ? fmaxf(v[r], 0.f) : v[r];
+            float* to = Cm + (int64_t)m * ldc + n;
+            if (VEC) {
+                *reinterpret_cast<v4f*>(to) = v;
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (n + r < n_real) to[r] = v[r];
             }
         }
+    }
+}
+
+// The layer on m particles: 128 x 256 tiles, or 128 x 64 where those would leave compute units idle (300 particles,
+// 512 -> 512: 6 blocks against 24).
+template <bool RELU>
+void dense(int M, int N, int K, const float* A, int lda, const bf16x8* ws, const float* bias, float* Cm, int ldc,
+           unsigned cus, hipStream_t stream)
+{
+    const unsigned mt = (unsigned)((M + 127) / 128);
+    if (mt * (unsigned)(N / 256) >= cus)
+        k_dense_split<4, 4, 2, 4, RELU, true><<<dim3(mt, N / 256), kDenseThreads, 0, stream>>>(M, N, N, K, A, lda, ws, bias, Cm, ldc);
+    else
+        k_dense_split<2, 2, 4, 2, RELU, true><<<dim3(mt, N / 64), kDenseThreads, 0, stream>>>(M, N, N, K, A, lda, ws, bias, Cm, ldc);
 }
 
 // The argmax of each particle's logits (the lowest class on ties) and its start element: the lookup element
@@ -458,7 +555,7 @@ void build_pool(cnnsns_mesh_s& m, hipStream_t stream)
 size_t cls_workspace_bytes(int64_t n)
 {
     const int64_t ch = n < kChunk ? n : kChunk;
-    return sizeof(float) * (size_t)ch * (size_t)(kNZ + kH2 + kNA);
+    return sizeof(bf16x8) * (size_t)(kD1 + kD2 + kD3) + sizeof(float) * (size_t)ch * (size_t)(kNZ + kH2 + kNA);
 }
 
 void run_classify(cnnsns_mesh_s& m, int64_t n, const double* xp, const cnnsns_cls& w, const int32_t* fallback,
@@ -469,23 +566,25 @@ void run_classify(cnnsns_mesh_s& m, int64_t n, const double* xp, const cnnsns_cl
     if (!m.cls_pool) build_pool(m, stream);
     workspace_acquire(m.cls_ws, cls_workspace_bytes(n), stream, "classify");
     const int64_t ch = n < kChunk ? n : kChunk;
-    float* Z = static_cast<float*>(m.cls_ws.ptr);     // [ch][512]: module 1 | module 2
+    bf16x8* wd = static_cast<bf16x8*>(m.cls_ws.ptr);   // the wide layers' weights
+    float* Z = reinterpret_cast<float*>(wd + kD1 + kD2 + kD3);  // [ch][512]: module 1 | module 2
     float* Hb = Z + ch * kNZ;                          // [ch][512]: module 2's first layer, then FC h2
     float* Lw = Hb + ch * kH2;                         // [ch][81] logits when the caller keeps none
     const auto* xp2 = reinterpret_cast<const double2*>(xp);
+    const unsigned cus = cnn_persistent_grid();
+    k_cls_prep<<<(kD1 + kD2 + kD3 + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[3], w.w[4], w.w[5], wd);
     for (int64_t c0 = 0; c0 < n; c0 += ch) {
         const int mc = (int)(n - c0 < ch ? n - c0 : ch);
         float* L = logits ? logits + c0 * kNA : Lw;
         // persistent: three blocks per compute unit fit its LDS
-        const unsigned mblocks = std::min<unsigned>(blocks_for(mc, kBlock / 64), cnn_persistent_grid() * 3);
+        const unsigned mblocks = std::min<unsigned>(blocks_for(mc, kBlock / 64), cus * 3);
         k_cls_module1<<<mblocks, kBlock, 0, stream>>>(
             mc, xp2 + c0, m.G, static_cast<const double2*>(m.cls_pool), w.w[0], w.b[0], w.w[1], w.b[1], w.w[2], w.b[2],
             Z, kNZ, Hb, kH2);
-        const dim3 g256(blocks_for(mc, kDT), kH1 / kDT), g512(blocks_for(mc, kDT), kH2 / kDT),
-            g81(blocks_for(mc, kDT), (kNA + kDT - 1) / kDT);
-        k_dense_f32<true><<<g256, kBlock, 0, stream>>>(mc, kH1, kH1, Hb, kH2, w.w[3], w.b[3], Z + kNF, kNZ);
-        k_dense_f32<true><<<g512, kBlock, 0, stream>>>(mc, kH2, kNZ, Z, kNZ, w.w[4], w.b[4], Hb, kH2);
-        k_dense_f32<false><<<g81, kBlock, 0, stream>>>(mc, kNA, kH2, Hb, kH2, w.w[5], w.b[5], L, kNA);
+        dense<true>(mc, kH1, kH1, Hb, kH2, wd, w.b[3], Z + kNF, kNZ, cus, stream);
+        dense<true>(mc, kH2, kNZ, Z, kNZ, wd + kD1, w.b[4], Hb, kH2, cus, stream);
+        k_dense_split<2, 3, 4, 2, false, false><<<dim3((mc + 127) / 128, 1), kDenseThreads, 0, stream>>>(
+            mc, kNL, kNA, kH2, Hb, kH2, wd + kD1 + kD2, w.b[5], L, kNA);
         k_cls_argmax<<<blocks_for(mc, kBlock), kBlock, 0, stream>>>(mc, xp2 + c0, m.G, m.lookup, L, kNA,
                                                                     fallback ? fallback + c0 : nullptr, start + c0,
                                                                     cls ? cls + c0 : nullptr);
