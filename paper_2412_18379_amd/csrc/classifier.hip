@@ -20,9 +20,8 @@
 // argmax), the lowest class on ties; class (dy + 4) 9 + (dx + 4) is the window
 // cell at offset (dx, dy) and K_p is that cell's overlay lookup element.
 //
-// On the GPU: one wavefront per particle for module 1 (window gather and
-// conv1 on the vector ALUs, conv2 on v_mfma_f32_16x16x4f32 with K ordered
-// tap-major, pooling) and module 2's first layer; the three wide FC layers as
+// On the GPU: one wavefront per particle for module 1 (window gather, both
+// convolutions on the matrix cores, pooling) and module 2's first layer; the three wide FC layers as
 // batched FP32 matrix products over a chunk of particles
 // (v_mfma_f32_16x16x4f32, 64 x 64 output tiles); then the argmax and start.
 #pragma clang fp contract(off)
@@ -39,7 +38,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kW = 9, kR = 4, kNA = kW * kW;  // window side, radius, classes
 constexpr int kC = 16;                         // conv channels
-constexpr int kPW = kW + 2;                    // the window with a one-cell zero border (conv padding)
+constexpr int kPW = kW + 2;                    // the window with a one-cell zero border (conv1's padding)
 constexpr int kNF = kC * 4 * 4;                // module 1 features (256)
 constexpr int kH1 = 256, kH2 = 512, kNZ = kNF + kH1;
 constexpr int kBlock = 256;
@@ -125,62 +124,103 @@ __global__ void k_pool_mean(int32_t G, const ElemRec* __restrict__ rec, const in
     pool[c] = p;
 }
 
-// Module 1 (window, conv1, conv2, pooling) and module 2's first layer, one wavefront per particle at a time
-// (persistent blocks loop over the particles with the weights staged once): writes
-// z[i][0 .. 255] and m1[i][0 .. 255] (row strides ldz, ldm).
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_cls_module1(
+// Module 1 and module 2's first layer, one wavefront per particle (persistent blocks).  conv1 (K = 18) runs on
+// the FP32 matrix instruction, all 81 cells; its output is split into three BF16 parts in LDS (split.h) and conv2
+// runs on those, K = 32 being two taps of 16 channels, for the 64 cells that the 2 x 2 pooling reads (the ninth
+// row and column are dropped): four blocks of 16, one for each place in a 2 x 2 pool, so that a lane holds all
+// four cells of its pool and averages them in registers.  Twelve wavefronts, three per SIMD, share conv2's
+// operands in LDS (kept in registers they spilled).
+//
+// What bounds it: matrix instructions (30 of 32 cycles and 120 of 16 a particle) and vector instructions, which add
+// up on a SIMD (cnn_rows.h).  With conv2 on the FP32 instruction over 96 cells, each of its accumulators written back
+// for the pooling, 65,536 particles took 364 us.
+constexpr int kMThreads = 768;
+constexpr int kMW = kW + 1;              // conv2's input: the window with a border of one, less the last row and column
+constexpr int kMPart = kMW * kMW * 2;    // bf16x8 of one part: two chunks of eight channels a cell
+
+// A cell's place, rows and columns from the border: even columns first, then the odd ones.  A lane of conv2 reads
+// every second cell, and a 16-lane group of a 16-byte read (lanes 0-7 with 56-63, ...) then covers 128 bytes
+// of two rows, at the two chunks of a cell: sixteen distinct places of the 64 banks.
+__host__ __device__ constexpr int m_place(int row, int c)
+{
+    return row * kMW + (c >> 1) + (c & 1) * (kMW / 2);
+}
+
+__global__ __launch_bounds__(kMThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_cls_module1(
     int64_t n, const double2* __restrict__ xp, int32_t G, const double2* __restrict__ pool,
     const float* __restrict__ w1, const float* __restrict__ b1, const float* __restrict__ w2,
     const float* __restrict__ b2, const float* __restrict__ wx1, const float* __restrict__ bx1,
     float* __restrict__ z, int ldz, float* __restrict__ m1, int ldm)
 {
-    constexpr int kWaves = kBlock / 64;
-    __shared__ float s_w1[kC * 2 * 9], s_b1[kC], s_b2[kC];
-    __shared__ float s_w2[9][kC][kC + 1];  // [tap][in channel][out channel], padded
+    constexpr int kWaves = kMThreads / 64;
+    __shared__ bf16x8 s_a1[kWaves][3 * kMPart];
+    __shared__ bf16x8 s_w2[5 * 3 * 64];
     __shared__ float s_in[kWaves][2][kPW * kPW];
-    // conv1's output on the bordered window; conv2's output goes to its interior once conv2 has read it
-    __shared__ float s_a1[kWaves][kPW * kPW][kC + 1];
-    __shared__ float s_x1[kH1][3];  // module 2's first layer: (w0, w1, bias) per output
+    __shared__ v4f s_x1[kH1 * 3 / 4];  // module 2's first layer: w0, w1, bias, kH1 of each
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int k = tid; k < kC * 2 * 9; k += kBlock) s_w1[k] = w1[k];
-    for (int k = tid; k < kC * kC * 9; k += kBlock) {
-        const int o = k / (kC * 9), i = (k / 9) % kC, t = k % 9;  // PyTorch [out][in][3][3]
-        s_w2[t][i][o] = w2[k];
-    }
-    if (tid < kC) {
-        s_b1[tid] = b1[tid];
-        s_b2[tid] = b2[tid];
-    }
-    for (int j = tid; j < kH1; j += kBlock) {
-        s_x1[j][0] = wx1[2 * j];
-        s_x1[j][1] = wx1[2 * j + 1];
-        s_x1[j][2] = bx1[j];
+    const int i = lane & 15, q = lane >> 4;
+    for (int j = tid; j < kH1; j += kMThreads) {
+        float* x1 = reinterpret_cast<float*>(s_x1);
+        x1[j] = wx1[2 * j];
+        x1[kH1 + j] = wx1[2 * j + 1];
+        x1[2 * kH1 + j] = bx1[j];
     }
     float* in = &s_in[wave][0][0];
+    bf16x8* a1 = &s_a1[wave][0];
     for (int k = lane; k < 2 * kPW * kPW; k += 64) in[k] = 0.f;
-    for (int k = lane; k < kPW * kPW * (kC + 1); k += 64) (&s_a1[wave][0][0])[k] = 0.f;
-    __syncthreads();  // the weights and the zero borders, which no point's writes touch
-    // a wavefront takes points i, i + the grid's wavefront count, ...: its window, conv1 output and
-    // conv2 output are its own LDS regions, so only the wavefront's own accesses need ordering
+    const bf16x8 none = __builtin_bit_cast(bf16x8, u32x4{ 0, 0, 0, 0 });
+    for (int k = lane; k < 3 * kMPart; k += 64) a1[k] = none;
+    // conv2's A operands: row = output channel l%16; lane group g of K step st takes tap 2 st + g/2 (zero past the
+    // ninth), channels 8 (g%2) + j
+    for (int k = tid; k < 5 * 3 * 64; k += kMThreads) {
+        const int l = k & 63, part = (k >> 6) % 3, t = 2 * (k / 192) + (l >> 5), c = 8 * ((l >> 4) & 1);
+        bf16x8 v;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = split_part(t < 9 ? w2[((l & 15) * kC + c + j) * 9 + t] : 0.f, part);
+        s_w2[k] = v;
+    }
+    __syncthreads();  // the weights, and the zero borders, which no point's writes touch
+    // a wavefront takes points p, p + the grid's wavefront count, ...: its window and conv1 output are its
+    // own LDS regions, so only the wavefront's own accesses need ordering
     auto wave_sync = [] {
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
     };
-    const int row = lane & 15, kq = lane >> 4;
-    int base[6];
-#pragma unroll
-    for (int mb = 0; mb < 6; ++mb) {
-        const int px = min(mb * 16 + row, kNA - 1), r = px / kW, c = px % kW;
-        base[mb] = r * kPW + c;  // top-left tap in the bordered window
-    }
-    // conv1's B operands: lane (row, kq) supplies output channel `row` at k = 4 st + kq = 9 ci + tap
+    // conv1: A operands (row = output channel i, k = 4 st + q = 9 ci + tap, zero for k >= 18) and the offsets of
+    // their inputs; the lane's cell of each 16-cell block (the last block repeats cell 80): where its window starts
+    // and where its result goes
     float w1k[5];
+    int off1[5], base[6], to[6];
 #pragma unroll
     for (int st = 0; st < 5; ++st) {
-        const int k = 4 * st + kq;
-        w1k[st] = k < 18 ? s_w1[(row * 2 + k / 9) * 9 + k % 9] : 0.f;
+        const int k = min(4 * st + q, 17), t = k % 9;
+        w1k[st] = 4 * st + q < 18 ? w1[i * 18 + k] : 0.f;
+        off1[st] = (k / 9) * kPW * kPW + (t / 3) * kPW + t % 3;
     }
+#pragma unroll
+    for (int mb = 0; mb < 6; ++mb) {
+        const int px = min(mb * 16 + i, kNA - 1), r = px / kW, c = px % kW;
+        base[mb] = r * kPW + c;
+        to[mb] = m_place(r + 1, c + 1);
+    }
+    // where the lane's pool i reads the tap of conv2's K step st, 2 st + q / 2, for the left and right cells of
+    // its upper row (the tenth tap has zero weights and reads the ninth's cell)
+    int at[5][2];
+#pragma unroll
+    for (int st = 0; st < 5; ++st)
+#pragma unroll
+        for (int dx = 0; dx < 2; ++dx) {
+            const int t = min(2 * st + (q >> 1), 8);
+            at[st][dx] = m_place(2 * (i >> 2) + t / 3, 2 * (i & 3) + dx + t % 3) * 2 + (q & 1);
+        }
+    v4f bias1, bias2;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        bias1[r] = b1[4 * q + r];
+        bias2[r] = b2[4 * q + r];
+    }
+
     // the window's pooled values of the wavefront's next particle are gathered into registers while
     // the current one computes (lane o holds window cells o and o + 64)
     const int64_t stride = (int64_t)gridDim.x * kWaves;
@@ -198,86 +238,94 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
             }
         }
     };
-    int64_t i = (int64_t)blockIdx.x * kWaves + wave;
-    if (i < n) gather(i);
-    for (; i < n; i += stride) {
+    int64_t p0 = (int64_t)blockIdx.x * kWaves + wave;
+    if (p0 < n) gather(p0);
+    for (; p0 < n; p0 += stride) {
         const double2 p = pn;
         const int32_t cx = cell_of(p.x, G), cy = cell_of(p.y, G);
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int o = lane + 64 * u;
             if (o < kNA) {
-                const int dy = o / kW - kR, dx = o % kW - kR;
-                const int at = (dy + kR + 1) * kPW + (dx + kR + 1);
-                in[at] = (float)((qn[u].x - p.x) * (double)G);
-                in[kPW * kPW + at] = (float)((qn[u].y - p.y) * (double)G);
+                const int at1 = (o / kW + 1) * kPW + (o % kW + 1);
+                in[at1] = (float)((qn[u].x - p.x) * (double)G);
+                in[kPW * kPW + at1] = (float)((qn[u].y - p.y) * (double)G);
             }
         }
         const float xo0 = (float)(p.x * (double)G - ((double)cx + 0.5));
         const float xo1 = (float)(p.y * (double)G - ((double)cy + 0.5));
         wave_sync();
-        if (i + stride < n) gather(i + stride);
-        // conv1 (2 -> 16) on the matrix cores: rows = pixels (6 blocks of 16, the last partly repeated),
-        // columns = output channels, k = 9 channel + tap (18, padded to 20: five steps of 4)
+        if (p0 + stride < n) gather(p0 + stride);
         {
-            v4f a1[6];
+            v4f acc[6];
 #pragma unroll
-            for (int mb = 0; mb < 6; ++mb) a1[mb] = v4f{ 0.f, 0.f, 0.f, 0.f };
+            for (int mb = 0; mb < 6; ++mb) acc[mb] = bias1;
 #pragma unroll
-            for (int st = 0; st < 5; ++st) {
-                const int k = 4 * st + kq, ci = k / 9, t = k % 9;
-                const int off = ci * kPW * kPW + (t / 3) * kPW + t % 3;
+            for (int st = 0; st < 5; ++st)
 #pragma unroll
-                for (int mb = 0; mb < 6; ++mb) {
-                    const float av = k < 18 ? in[base[mb] + off] : 0.f;
-                    a1[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, w1k[st], a1[mb], 0, 0, 0);
+                for (int mb = 0; mb < 6; ++mb)
+                    acc[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w1k[st], in[base[mb] + off1[st]], acc[mb], 0, 0, 0);
+            // lane: channels 4q + r of its cell
+#pragma unroll
+            for (int mb = 0; mb < 6; ++mb) {
+                u32x2 h, m, l;
+                uint32_t ph, pm, pl;
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    split_pair(fmaxf(acc[mb][2 * j], 0.f), fmaxf(acc[mb][2 * j + 1], 0.f), ph, pm, pl);
+                    h[j] = ph;
+                    m[j] = pm;
+                    l[j] = pl;
                 }
+                u32x2* dst = reinterpret_cast<u32x2*>(a1) + to[mb] * 4 + q;
+                dst[0] = h;
+                dst[2 * kMPart] = m;
+                dst[4 * kMPart] = l;
             }
-            // lane holds pixels 16 mb + 4 kq + e of output channel `row`
-#pragma unroll
-            for (int mb = 0; mb < 6; ++mb)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int px = mb * 16 + 4 * kq + e;
-                    if (px < kNA)
-                        s_a1[wave][(px / kW + 1) * kPW + px % kW + 1][row] = fmaxf(a1[mb][e] + s_b1[row], 0.f);
-                }
         }
         wave_sync();
-        // conv2 (16 -> 16) on the matrix cores: rows = pixels (6 blocks of 16, the last partly
-        // repeated), columns = output channels, k = 16 tap + input channel in 36 steps of 4
-        v4f acc[6];
+        v4f hi[4], lo[4];
 #pragma unroll
-        for (int mb = 0; mb < 6; ++mb) acc[mb] = v4f{ 0.f, 0.f, 0.f, 0.f };
-        for (int s = 0; s < 36; ++s) {
-            const int t = s >> 2, ch = 4 * (s & 3) + kq;
-            const int off = (t / 3) * kPW + t % 3;
-            const float bw = s_w2[t][ch][row];
-#pragma unroll
-            for (int mb = 0; mb < 6; ++mb)
-                acc[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(s_a1[wave][base[mb] + off][ch], bw, acc[mb], 0, 0, 0);
+        for (int m = 0; m < 4; ++m) {
+            hi[m] = bias2;
+            lo[m] = v4f{ 0.f, 0.f, 0.f, 0.f };
         }
-        wave_sync();  // conv2 has read all of conv1's output
-        // lane holds pixels 16 mb + 4 kq + e of output channel `row`: into the interior of the window
 #pragma unroll
-        for (int mb = 0; mb < 6; ++mb)
+        for (int st = 0; st < 5; ++st) {
+            bf16x8 x[4][3];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int px = mb * 16 + 4 * kq + e;
-                if (px < kNA) s_a1[wave][(px / kW + 1) * kPW + px % kW + 1][row] = fmaxf(acc[mb][e] + s_b2[row], 0.f);
-            }
-        wave_sync();
+            for (int m = 0; m < 4; ++m)  // m = 2 dy + dx
+#pragma unroll
+                for (int part = 0; part < 3; ++part)
+                    x[m][part] = a1[at[st][m & 1] + (m >> 1) * kMW * 2 + part * kMPart];
+            bf16x8 w[3];
+#pragma unroll
+            for (int part = 0; part < 3; ++part) w[part] = s_w2[(st * 3 + part) * 64 + lane];
+            constexpr int wp[6] = { 0, 0, 1, 1, 0, 2 }, xq[6] = { 0, 1, 0, 1, 2, 0 };
+#pragma unroll
+            for (int k = 0; k < 6; ++k)
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    v4f& acc = k == 0 ? hi[m] : lo[m];
+                    acc = mfma_bf16(w[wp[k]], x[m][xq[k]], acc);
+                }
+        }
         // 2 x 2 average pooling, [channel][row][col] order
-        for (int f = lane; f < kNF; f += 64) {
-            const int ch = f >> 4, pr = (f >> 2) & 3, pc = f & 3;
-            const int p0 = (2 * pr + 1) * kPW + 2 * pc + 1;
-            const float q = ((s_a1[wave][p0][ch] + s_a1[wave][p0 + 1][ch]) + s_a1[wave][p0 + kPW][ch]) +
-                            s_a1[wave][p0 + kPW + 1][ch];
-            z[i * ldz + f] = q * 0.25f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float y[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) y[m] = fmaxf(hi[m][r] + lo[m][r], 0.f);
+            z[p0 * ldz + (4 * q + r) * 16 + i] = (((y[0] + y[1]) + y[2]) + y[3]) * 0.25f;
         }
-        // module 2, first layer: FC 2 -> 256 on x_p's offset
-        for (int j = lane; j < kH1; j += 64)
-            m1[i * ldm + j] = fmaxf(s_x1[j][2] + s_x1[j][0] * xo0 + s_x1[j][1] * xo1, 0.f);
+        // module 2, first layer: FC 2 -> 256 on x_p's offset, outputs 4 lane ..
+        {
+            const v4f wa = s_x1[lane], wb = s_x1[kH1 / 4 + lane], bx = s_x1[kH1 / 2 + lane];
+            v4f v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = fmaxf(bx[r] + wa[r] * xo0 + wb[r] * xo1, 0.f);
+            *reinterpret_cast<v4f*>(m1 + p0 * ldm + 4 * lane) = v;
+        }
         wave_sync();  // the next point's window and conv1 output replace these
     }
 }
@@ -576,9 +624,9 @@ void run_classify(cnnsns_mesh_s& m, int64_t n, const double* xp, const cnnsns_cl
     for (int64_t c0 = 0; c0 < n; c0 += ch) {
         const int mc = (int)(n - c0 < ch ? n - c0 : ch);
         float* L = logits ? logits + c0 * kNA : Lw;
-        // persistent: three blocks per compute unit fit its LDS
-        const unsigned mblocks = std::min<unsigned>(blocks_for(mc, kBlock / 64), cus * 3);
-        k_cls_module1<<<mblocks, kBlock, 0, stream>>>(
+        // persistent: one block per compute unit
+        const unsigned mblocks = std::min<unsigned>(blocks_for(mc, kMThreads / 64), cus);
+        k_cls_module1<<<mblocks, kMThreads, 0, stream>>>(
             mc, xp2 + c0, m.G, static_cast<const double2*>(m.cls_pool), w.w[0], w.b[0], w.w[1], w.b[1], w.w[2], w.b[2],
             Z, kNZ, Hb, kH2);
         dense<true>(mc, kH1, kH1, Hb, kH2, wd, w.b[3], Z + kNF, kNZ, cus, stream);
