@@ -725,7 +725,7 @@ unsigned cnn_persistent_grid()
 // worth, so the row form loses where its segments are a few rows long; below that, at one row a segment,
 // the tile form's single tile for a part of the compute units takes longer.  Kernels of a pass in us, tile and
 // row form: G = 33: 40.8 and 35.9, 128: 41.8 and 38.8, 160: 42.2 and 49.1, 512: 93 and 98, 700: 152 and 147,
-// 800: 181 and 187, 900: 239 and 210, 1024: 283 and 236, 1531: 583 and 495.
+// 800: 181 and 187, 900: 239 and 210, 1024: 283 and 232, 1531: 583 and 479.
 static bool rows_form(int32_t G)
 {
     return G <= 128 || G >= 832;

@@ -34,6 +34,7 @@
 #pragma once
 
 #include "common.h"
+#include "lds_copy.h"
 #include "split.h"
 
 namespace cnnsns {
@@ -562,8 +563,7 @@ static __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu
             const float* from = (unsigned)gx < (unsigned)G && (unsigned)a < (unsigned)G ? src + (int64_t)gx * C + 4 * (pc & 7)
                                                            : reinterpret_cast<const float*>(ws + kOffZero);
             if (k < ROWV)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)from,
-                                                 (__attribute__((address_space(3))) void*)(s_row[a & 1] + p0 * 64), 16, 0, 0);
+                lds_copy16(from, s_row[a & 1] + p0 * 64);
         };
         static_assert((ROWV + 63) / 64 == 4 * kWaves + 1, "four pieces per wavefront and one in turn");
 #pragma unroll
@@ -577,7 +577,7 @@ static __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu
     if (tid < 2 * C) reinterpret_cast<float*>(s_b)[tid] = tid < C ? b3[tid] : -b3[tid - C];
     if (tid < 2 * kWaves * 4) (&s_side[0][0][0])[tid] = 0.f;  // wavefronts past the grid leave theirs at zero
     const float bias4[2] = { b4[0], b4[1] };
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    lds_copies_arrived();
     __syncthreads();
 
     v4f part[2][2];      // [column e][component o]: running sums for three output rows
@@ -685,7 +685,7 @@ static __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu
             }
         }
         if (active && a <= r1 + 1) rc.stages<0, kTail>(c2, c0, c1);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the row has arrived
+        lds_copies_arrived();  // the row has arrived
         __syncthreads();
     };
     Acc c0, c1, c2;
