@@ -29,6 +29,7 @@
 #include <hipcub/hipcub.hpp>
 
 #include "common.h"
+#include "lds_copy.h"
 #include "split.h"
 
 namespace cnnsns {
@@ -337,8 +338,11 @@ __global__ __launch_bounds__(kMThreads) __attribute__((amdgpu_waves_per_eu(3, 3)
 // own.  K goes in slices of 32, double-buffered in LDS: the weights' operands are copied straight into LDS as
 // prepared (k_cls_prep), the activations are loaded into registers, split and written after the slice's products.
 //
-// What bounds it: matrix instructions, 96 per wavefront and slice (16.5 cycles each) at 128 x 256.  65,536
-// particles: 512 -> 512 took 0.36 ms on the FP32 instruction in 128 x 128 tiles.
+// What bounds it: matrix instructions, 96 per wavefront and slice (16.5 cycles each) at 128 x 256, 1.5 us of the
+// 3.2 a slice takes; the rest is the splitting, the LDS reads and the barrier, which one block per compute unit
+// does not hide.  65,536 particles, 512 -> 512: 0.21 ms, 0.36 on the FP32 instruction in 128 x 128 tiles.  One kernel
+// for all three layers with the activations passed on already split took 0.30 ms against 0.31 for the three, and
+// 69 us against 46 at 300 particles, where a block's serial chain of slices is all that counts.
 constexpr int kDenseThreads = 512;
 
 // Operand-ordered split weights of a layer with N (padded to 16) outputs and K inputs:
@@ -397,8 +401,7 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
     auto load_w = [&](int ks) {
         const bf16x8* src = ws + ((int64_t)ks * (N / 16) + n0 / 16) * 192 + lane;
         for (int f = wave; f < NF; f += 8)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + f * 64),
-                                             (__attribute__((address_space(3))) void*)(s_w[ks & 1] + f * 64), 16, 0, 0);
+            lds_copy16(src + f * 64, s_w[ks & 1] + f * 64);
     };
     v4f pa[PER];
     auto fetch = [&](int ks) {
@@ -444,7 +447,7 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
     load_w(0);
     fetch(0);
     stash(0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the weights have arrived
+    lds_copies_arrived();  // the weights have arrived
     __syncthreads();
     const int slices = K / 32;
     for (int ks = 0; ks < slices; ++ks) {
@@ -473,7 +476,7 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
                     acc = mfma_bf16(w[nb][wp[k]], x[mb][xp[k]], acc);
                 }
         if (ks + 1 < slices) stash(ks + 1);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        lds_copies_arrived();
         __syncthreads();
     }
 #pragma unroll
@@ -498,17 +501,22 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
     }
 }
 
-// The layer on m particles: 128 x 256 tiles, or 128 x 64 where those would leave compute units idle (300 particles,
-// 512 -> 512: 6 blocks against 24).
+// The layer on M particles: 128 x 256 tiles while they fill the chip, 128 x 64 tiles for a last round that would
+// leave most compute units idle.  A round of the large tiles takes 51 us (512 -> 512), one of the small ones, four
+// times as many blocks, 16: the small ones are the faster up to three rounds.
 template <bool RELU>
 void dense(int M, int N, int K, const float* A, int lda, const bf16x8* ws, const float* bias, float* Cm, int ldc,
            unsigned cus, hipStream_t stream)
 {
-    const unsigned mt = (unsigned)((M + 127) / 128);
-    if (mt * (unsigned)(N / 256) >= cus)
-        k_dense_split<4, 4, 2, 4, RELU, true><<<dim3(mt, N / 256), kDenseThreads, 0, stream>>>(M, N, N, K, A, lda, ws, bias, Cm, ldc);
-    else
-        k_dense_split<2, 2, 4, 2, RELU, true><<<dim3(mt, N / 64), kDenseThreads, 0, stream>>>(M, N, N, K, A, lda, ws, bias, Cm, ldc);
+    const unsigned mt = (unsigned)((M + 127) / 128), nb = (unsigned)N / 256;
+    unsigned large = mt - mt % std::max(cus / nb, 1u);  // row tiles in whole rounds
+    if ((mt - large) * 4 * nb > 3 * cus) large = mt;
+    const int rows = (int)std::min<unsigned>(large * 128, (unsigned)M);
+    if (large)
+        k_dense_split<4, 4, 2, 4, RELU, true><<<dim3(large, nb), kDenseThreads, 0, stream>>>(rows, N, N, K, A, lda, ws, bias, Cm, ldc);
+    if (large < mt)
+        k_dense_split<2, 2, 4, 2, RELU, true><<<dim3(mt - large, N / 64), kDenseThreads, 0, stream>>>(
+            M - rows, N, N, K, A + (int64_t)rows * lda, lda, ws, bias, Cm + (int64_t)rows * ldc, ldc);
 }
 
 // The argmax of each particle's logits (the lowest class on ties) and its start element: the lookup element
