@@ -1,0 +1,47 @@
+"""GPU: the BF16 forward pass, which walks down strips of 122 output columns, where its tiling has edges: one row and
+column, one strip less, exactly and more than full, a strip of one column, and strips laid end to end with blocks
+that cross from one to the next (G = 2320).  Bars of test_gpu_cnn.py, and the same bits wherever a pixel lies in a
+strip: the pass over a window of the grid equals the pass over the whole of it, off the window's four-pixel border.
+"""
+import gc
+
+import numpy as np
+import pytest
+import torch
+
+from test_gpu_cnn import BF16_MAX, BF16_MEAN, _bf16_errors, _dev, _square_mesh
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def C():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2412_18379_amd import cnnsns
+    cnnsns.lib()
+    yield cnnsns
+    gc.collect()
+
+
+@pytest.mark.parametrize("G", [2, 3, 121, 122, 123, 125, 244, 245, 2320])
+def test_bf16_strip_edges(C, oracle_mod, wl, G):
+    rng = np.random.default_rng(G)
+    vel = rng.standard_normal((2, G, G)).astype(np.float32)
+    ws, bs = wl.random_weights(G)
+    W = C.Weights(ws, bs)
+
+    def predict(v):
+        mesh = _square_mesh(C, v.shape[1])
+        out = C.predict(mesh, _dev(v), W, "bf16").cpu().numpy()
+        mesh.close()
+        return out
+
+    disp = predict(vel)
+    if G <= 245:
+        emax, emean = _bf16_errors(disp, oracle_mod.cnn_forward(vel, ws, bs))
+        assert emax <= BF16_MAX and emean <= BF16_MEAN, (emax, emean)
+    n = min(G - 37, 300)
+    for y, x in ((37, 5), (G - n, G - n), (11, (G - n) // 2)) if n > 8 else ():
+        part = predict(np.ascontiguousarray(vel[:, y:y + n, x:x + n]))
+        assert np.array_equal(part[:, 4:-4, 4:-4], disp[:, y + 4:y + n - 4, x + 4:x + n - 4])
