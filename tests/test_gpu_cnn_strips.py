@@ -1,7 +1,8 @@
-"""GPU: the BF16 forward pass, which walks down strips of 122 output columns, where its tiling has edges: one row and
-column, one strip less, exactly and more than full, a strip of one column, and strips laid end to end with blocks
+"""GPU: the BF16 and FP8 forward passes, which walk down strips of 122 output columns, where their tiling has edges: a few
+rows and columns, one strip less, exactly and more than full, a strip of one column, and strips laid end to end with blocks
 that cross from one to the next (G = 2320).  Bars of test_gpu_cnn.py, and the same bits wherever a pixel lies in a
-strip: the pass over a window of the grid equals the pass over the whole of it, off the window's four-pixel border.
+strip: the pass over a window of the grid equals the pass over the whole of it, off the window's four-pixel border (for
+FP8 with the same largest velocity in both, from which its scales follow; its accuracy is tested elsewhere).
 """
 import gc
 
@@ -25,20 +26,22 @@ def C():
 
 
 @pytest.mark.parametrize("G", [2, 3, 121, 122, 123, 125, 244, 245, 2320])
-def test_bf16_strip_edges(C, oracle_mod, wl, G):
+@pytest.mark.parametrize("precision", ["bf16", "fp8"])
+def test_strip_edges(C, oracle_mod, wl, precision, G):
     rng = np.random.default_rng(G)
-    vel = rng.standard_normal((2, G, G)).astype(np.float32)
+    vel = np.clip(rng.standard_normal((2, G, G)), -4.0, 4.0).astype(np.float32)
+    vel[:, ::25, ::25] = 4.0
     ws, bs = wl.random_weights(G)
     W = C.Weights(ws, bs)
 
     def predict(v):
         mesh = _square_mesh(C, v.shape[1])
-        out = C.predict(mesh, _dev(v), W, "bf16").cpu().numpy()
+        out = C.predict(mesh, _dev(v), W, precision).cpu().numpy()
         mesh.close()
         return out
 
     disp = predict(vel)
-    if G <= 245:
+    if G <= 245 and precision == "bf16":
         emax, emean = _bf16_errors(disp, oracle_mod.cnn_forward(vel, ws, bs))
         assert emax <= BF16_MAX and emean <= BF16_MEAN, (emax, emean)
     n = min(G - 37, 300)
