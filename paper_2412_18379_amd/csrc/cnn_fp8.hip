@@ -26,16 +26,14 @@ using namespace strips;
 
 typedef long fp8x8;  // eight e4m3 values, the k = 8 (l/16) + j operand slots of lane l
 
-// Scales and the per-channel epilogue factors, written by k_fp8_prep
+// What the forward pass forms its scales from, written by k_fp8_scan
+constexpr int kMaxBlocks = 160;  // what the workspace of 21.5 KiB has room for
 struct Fp8Scales {
-    unsigned vmax_bits;       // max |u|, |v| over the grid (bit pattern of a non-negative float)
-    float s_v;                // velocity scale
-    float s_a[3];             // activation scales after layers 1..3
+    float vmax[kMaxBlocks];   // max |u|, |v| over a block's share of the grid
     float s_w[4][C];          // weight scale per layer and output channel (layer 4: channels 0, 1)
-    float init[3][C];         // accumulator start b_o / (s_w,o s_in) of layers 1..3
-    float fac[3][C];          // s_w,o s_in / s_out of layers 1..3
-    float out4[2];            // s_w4,o s_a3
+    float rsum[3][C];         // sum of |w| over inputs and taps, layers 1..3
 };
+static_assert(sizeof(fp8x8) * PACKED + sizeof(Fp8Scales) <= 22016, "the workspace that the interface states");
 
 __device__ __forceinline__ float pow2_at_least(float x)
 {
@@ -51,63 +49,53 @@ __device__ __forceinline__ uint32_t to_e4m3_pair(float lo, float hi)
     return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(lo, hi, 0, false) & 0xffffu;
 }
 
-__global__ void k_fp8_clear(Fp8Scales* s)
+// One launch for what the pass needs of the weights and of the whole grid.  Blocks 0 .. 5: layer 1, the halves of 16
+// output channels of layers 2 and 3, layer 4: each stages its FP32 weights in LDS, a wavefront reduces the max and the
+// sum of |w| of an output channel, and all threads pack.  The others: max |u|, |v| of their share of the 2 G^2 velocity
+// values.  The chain of activation bounds, which needs both, is a few instructions at the pass's start.  With a clear,
+// one atomic maximum a block and a one-block kernel for weights and chain instead: 21 us at G = 64, 30 at 1531 and 61 at
+// 4096; now 5, 5 and 20, and 2 us more in the pass.
+constexpr int kScanThreads = 1024, kWeightBlocks = 6;
+__global__ __launch_bounds__(kScanThreads) void k_fp8_scan(const float* __restrict__ w1, const float* __restrict__ w2,
+                                                           const float* __restrict__ w3, const float* __restrict__ w4,
+                                                           int64_t count, const float* __restrict__ vel,
+                                                           Fp8Scales* __restrict__ s, fp8x8* __restrict__ packed)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) s->vmax_bits = 0u;
-}
-
-// max |u|, |v| over the 2 G^2 velocity values: a block reduces its share through LDS and makes one
-// atomic update (one per wavefront on a single word serialises thousands of updates)
-constexpr int kMaxThreads = 512;
-__global__ __launch_bounds__(kMaxThreads) void k_fp8_absmax(int64_t count, const float* __restrict__ vel, Fp8Scales* s)
-{
-    __shared__ float s_m[kMaxThreads / 64];
-    float m = 0.f;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < count; k += (int64_t)gridDim.x * blockDim.x)
-        m = fmaxf(m, fabsf(vel[k]));
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-    if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < kMaxThreads / 64; ++w) m = fmaxf(m, s_m[w]);
-        atomicMax(&s->vmax_bits, __float_as_uint(m));
+    __shared__ float s_w[16 * C * 9];
+    __shared__ float s_x[C];  // weight scale per output channel, or the wavefronts' maxima
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b = blockIdx.x;
+    if (b >= kWeightBlocks) {
+        const int64_t step = (int64_t)(gridDim.x - kWeightBlocks) * kScanThreads;
+        int64_t k = (int64_t)(b - kWeightBlocks) * kScanThreads + tid;
+        // four at a time, from the first 16-byte boundary on; the values before it and past the last four one by one
+        const int64_t head = std::min<int64_t>(count, (16 - ((uintptr_t)vel & 15)) % 16 / 4), quads = (count - head) / 4;
+        const v4f* from = reinterpret_cast<const v4f*>(vel + head);
+        float m = 0.f;
+        if (k < head) m = fabsf(vel[k]);
+        if (head + 4 * quads + k < count) m = fmaxf(m, fabsf(vel[head + 4 * quads + k]));
+#pragma unroll 4
+        for (; k < quads; k += step) {
+            const v4f x = from[k];
+            m = fmaxf(fmaxf(fmaxf(m, fabsf(x[0])), fmaxf(fabsf(x[1]), fabsf(x[2]))), fabsf(x[3]));
+        }
+        for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+        if (lane == 0) s_x[wave] = m;
+        __syncthreads();
+        if (tid == 0) {
+            for (int w = 1; w < kScanThreads / 64; ++w) m = fmaxf(m, s_x[w]);
+            s->vmax[b - kWeightBlocks] = m;
+        }
+        return;
     }
-}
-
-// Weight scales, activation scales and the packed e4m3 weights; one block of 1024 threads.  The
-// FP32 weights are staged in LDS (78 KiB), each wavefront reduces the max and the sum of |w| of
-// its output channels, the first wavefront chains the layer bounds (one lane per channel), and
-// all threads pack.
-constexpr int NW1 = C * 2 * 9, NW23 = C * C * 9, NW4 = 2 * C * 9;
-__global__ __launch_bounds__(1024) void k_fp8_prep(const float* __restrict__ w1, const float* __restrict__ w2,
-                                                   const float* __restrict__ w3, const float* __restrict__ w4,
-                                                   const float* __restrict__ b1, const float* __restrict__ b2,
-                                                   const float* __restrict__ b3, Fp8Scales* s,
-                                                   fp8x8* __restrict__ packed)
-{
-    __shared__ float s_w[NW1 + 2 * NW23 + NW4];
-    __shared__ float s_rsum[3][C];   // sum of |w| over inputs and taps per output channel, layers 1..3
-    __shared__ float s_scale[4][C];  // weight scale per layer and output channel
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    float* const sw1 = s_w;
-    float* const sw2 = sw1 + NW1;
-    float* const sw3 = sw2 + NW23;
-    float* const sw4 = sw3 + NW23;
-    for (int k = tid; k < NW1; k += 1024) sw1[k] = w1[k];
-    for (int k = tid; k < NW23; k += 1024) {
-        sw2[k] = w2[k];
-        sw3[k] = w3[k];
-    }
-    for (int k = tid; k < NW4; k += 1024) sw4[k] = w4[k];
+    const int layer = b == 0 ? 0 : b == 5 ? 3 : (b + 1) / 2, c0 = b == 2 || b == 4 ? 16 : 0;  // first channel
+    const int channels = b == 0 ? C : b == 5 ? 2 : 16, per = (layer == 0 ? 2 : C) * 9;
+    const float* w = (layer == 0 ? w1 : layer == 1 ? w2 : layer == 2 ? w3 : w4) + c0 * per;
+    for (int k = tid; k < channels * per; k += kScanThreads) s_w[k] = w[k];
     __syncthreads();
-    // channel c = 0 .. 97: layer c / 32 (layer 4: c = 96, 97), output channel c % 32
-    for (int c = wave; c < 3 * C + 2; c += 16) {
-        const int l = c < 3 * C ? c / C : 3, o = c < 3 * C ? c % C : c - 3 * C;
-        const float* w = l == 0 ? sw1 : (l == 1 ? sw2 : (l == 2 ? sw3 : sw4));
-        const int per = (l == 0 ? 2 : C) * 9;
+    for (int o = wave; o < channels; o += kScanThreads / 64) {
         float mx = 0.f, sm = 0.f;
         for (int k = lane; k < per; k += 64) {
-            const float a = fabsf(w[o * per + k]);
+            const float a = fabsf(s_w[o * per + k]);
             mx = fmaxf(mx, a);
             sm += a;
         }
@@ -116,63 +104,36 @@ __global__ __launch_bounds__(1024) void k_fp8_prep(const float* __restrict__ w1,
             sm += __shfl_xor(sm, off);
         }
         if (lane == 0) {
-            s_scale[l][o] = pow2_at_least(mx / 448.f);
-            if (l < 3) s_rsum[l][o] = sm;
+            s->s_w[layer][c0 + o] = s_x[o] = pow2_at_least(mx / 448.f);
+            if (layer < 3) s->rsum[layer][c0 + o] = sm;
         }
     }
     __syncthreads();
-    if (wave == 0) {
-        const float margin = 1.25f;  // covers the rounding of operands (at most 2^-4 each)
-        const int o = lane & (C - 1);
-        const float bl[3] = { b1[o], b2[o], b3[o] };
-        float A = __uint_as_float(s->vmax_bits);
-        float s_in = pow2_at_least(A / 448.f);
-        if (lane == 0) s->s_v = s_in;
-        for (int l = 0; l < 3; ++l) {
-            float P = margin * s_rsum[l][o] * A + fabsf(bl[l]);
-            for (int off = 16; off > 0; off >>= 1) P = fmaxf(P, __shfl_xor(P, off));
-            const float s_out = pow2_at_least(P / 448.f);
-            if (lane < C) {
-                const float sc = s_scale[l][o] * s_in;
-                s->s_w[l][o] = s_scale[l][o];
-                s->init[l][o] = bl[l] / sc;
-                s->fac[l][o] = sc / s_out;
-            }
-            if (lane == 0) s->s_a[l] = s_out;
-            A = P;
-            s_in = s_out;
-        }
-        if (lane < 2) {
-            s->s_w[3][lane] = s_scale[3][lane];
-            s->out4[lane] = s_scale[3][lane] * s_in;
-        }
-    }
-    for (int e = tid; e < PACKED; e += 1024) {
+    // layers 2 and 3: the half's fragments are every second one of the layer's
+    fp8x8* to = packed + (layer == 0 ? 0 : layer == 3 ? P1 + 2 * P2 : P1 + (layer - 1) * P2);
+    const int n = layer == 0 || layer == 3 ? 2 * 64 : 9 * 64;
+    for (int e = tid; e < n; e += kScanThreads) {
         const int l = e & 63, i = l & 15, q = l >> 4;
         float v[8];
-        if (e < P1) {
+        if (layer == 0) {
             const int o = (e >> 6) * 16 + i;
-            const float r = 1.f / s_scale[0][o];
+            const float r = 1.f / s_x[o];
             for (int j = 0; j < 8; ++j) {
                 const int k = 8 * q + j;
-                v[j] = k < 18 ? sw1[(o * 2 + (k & 1)) * 9 + (k >> 1)] * r : 0.f;
+                v[j] = k < 18 ? s_w[(o * 2 + (k & 1)) * 9 + (k >> 1)] * r : 0.f;
             }
-        } else if (e < P1 + 2 * P2) {
-            const int f = e - P1;
-            const int layer = f < P2 ? 1 : 2;
-            const float* w = f < P2 ? sw2 : sw3;
-            const int g = f % P2, t = g / 128, o = ((g >> 6) & 1) * 16 + i;
-            const float r = 1.f / s_scale[layer][o];
-            for (int j = 0; j < 8; ++j) v[j] = w[(o * C + chan_at(8 * q + j)) * 9 + t] * r;
+        } else if (layer < 3) {
+            const float r = 1.f / s_x[i];
+            for (int j = 0; j < 8; ++j) v[j] = s_w[(i * C + chan_at(8 * q + j)) * 9 + (e >> 6)] * r;
         } else {
             int o, tap;
-            const bool used = conv4_row(16 * ((e - P1 - 2 * P2) >> 6) + i, o, tap);
-            const float r = 1.f / s_scale[3][o];
-            for (int j = 0; j < 8; ++j) v[j] = used ? sw4[(o * C + chan_at(8 * q + j)) * 9 + tap] * r : 0.f;
+            const bool used = conv4_row(16 * (e >> 6) + i, o, tap);
+            const float r = 1.f / s_x[o];
+            for (int j = 0; j < 8; ++j) v[j] = used ? s_w[(o * C + chan_at(8 * q + j)) * 9 + tap] * r : 0.f;
         }
         uint64_t word = 0;
         for (int j = 0; j < 8; j += 2) word |= (uint64_t)to_e4m3_pair(v[j], v[j + 1]) << (8 * j);
-        packed[e] = (fp8x8)word;
+        to[layer == 0 || layer == 3 ? e : (2 * (e >> 6) + (c0 >> 4)) * 64 + l] = (fp8x8)word;
     }
 }
 
@@ -181,22 +142,41 @@ struct Fp8 {
     static constexpr int BYTES = 32;
     struct Args {
         const Fp8Scales* sc;
-        const float* b4;
+        int maxima;  // of sc->vmax
+        const float *b1, *b2, *b3, *b4;
     };
     v4f start[2][2], fac[2][2];
     float rv, out4, bo, sum0;
 
-    __device__ __forceinline__ Fp8(const Args& a, bool first, int q, int o)
-        : rv(1.f / a.sc->s_v), out4(a.sc->out4[o]), bo(a.b4[o]), sum0(0.f)
+    // the layers' bounds and scales, lane % 32 = output channel, and of these the lane's constants
+    __device__ __forceinline__ Fp8(const Args& a, bool first, int q, int oo) : bo(a.b4[oo]), sum0(0.f)
     {
+        const float margin = 1.25f;  // covers the rounding of operands (at most 2^-4 each)
+        const int lane = threadIdx.x & 63, o = lane & (C - 1);
+        const float bl[3] = { a.b1[o], a.b2[o], a.b3[o] };
+        float A = 0.f;
+        for (int k = lane; k < a.maxima; k += 64) A = fmaxf(A, a.sc->vmax[k]);
+        for (int off = 32; off > 0; off >>= 1) A = fmaxf(A, __shfl_xor(A, off));
+        float s_in = pow2_at_least(A / 448.f), init[2], scale[2];
+        rv = 1.f / s_in;
 #pragma unroll
-        for (int l = 0; l < 2; ++l) {
-            const int layer = l == 0 ? 0 : first ? 1 : 2;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                start[l][k >> 2][k & 3] = a.sc->init[layer][16 * (k >> 2) + 4 * q + (k & 3)];
-                fac[l][k >> 2][k & 3] = a.sc->fac[layer][16 * (k >> 2) + 4 * q + (k & 3)];
+        for (int l = 0; l < 3; ++l) {
+            float P = margin * a.sc->rsum[l][o] * A + fabsf(bl[l]);
+            for (int off = 16; off > 0; off >>= 1) P = fmaxf(P, __shfl_xor(P, off));
+            const float s_out = pow2_at_least(P / 448.f), sc = a.sc->s_w[l][o] * s_in;
+            if (l == 0 || l == (first ? 1 : 2)) {
+                init[l != 0] = bl[l] / sc;
+                scale[l != 0] = sc / s_out;
             }
+            A = P;
+            s_in = s_out;
+        }
+        out4 = a.sc->s_w[3][oo] * s_in;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int c = 16 * (k >> 2 & 1) + 4 * q + (k & 3);
+            start[k >> 3][k >> 2 & 1][k & 3] = __shfl(init[k >> 3], c);
+            fac[k >> 3][k >> 2 & 1][k & 3] = __shfl(scale[k >> 3], c);
         }
     }
     // A store of 16 consecutive pixels at one chunk, and a read of these at two, fall on distinct banks.
@@ -246,12 +226,11 @@ void cnn_fp8_forward(int32_t G, const float* vel, const cnnsns_cnn& w, float* di
     fp8x8* packed = static_cast<fp8x8*>(ws);
     Fp8Scales* sc = reinterpret_cast<Fp8Scales*>(static_cast<char*>(ws) + sizeof(fp8x8) * (size_t)PACKED);
     const int64_t count = 2 * (int64_t)G * G;
-    k_fp8_clear<<<1, 64, 0, stream>>>(sc);
-    const unsigned rb = (unsigned)std::min<int64_t>(512, std::max<int64_t>(1, (count + kMaxThreads - 1) / kMaxThreads));
-    k_fp8_absmax<<<rb, kMaxThreads, 0, stream>>>(count, vel, sc);
-    k_fp8_prep<<<1, 1024, 0, stream>>>(w.w[0], w.w[1], w.w[2], w.w[3], w.b[0], w.b[1], w.b[2], sc, packed);
+    const int blocks = (int)std::min<int64_t>(kMaxBlocks, (count + 4 * kScanThreads - 1) / (4 * kScanThreads));
+    k_fp8_scan<<<kWeightBlocks + blocks, kScanThreads, 0, stream>>>(w.w[0], w.w[1], w.w[2], w.w[3], count, vel, sc, packed);
     const Plan plan = strip_rows(G, (int)grid);
-    k_cnn_fp8<<<(plan.blocks + 7) / 8 * 8, kThreads, 0, stream>>>(G, plan, vel, packed, Fp8::Args{ sc, w.b[3] }, disp);
+    k_cnn_fp8<<<(plan.blocks + 7) / 8 * 8, kThreads, 0, stream>>>(
+        G, plan, vel, packed, Fp8::Args{ sc, blocks, w.b[0], w.b[1], w.b[2], w.b[3] }, disp);
     hip_check(hipGetLastError(), "fp8 cnn launch");
 }
 

@@ -48,3 +48,26 @@ def test_strip_edges(C, oracle_mod, wl, precision, G):
     for y, x in ((37, 5), (G - n, G - n), (11, (G - n) // 2)) if n > 8 else ():
         part = predict(np.ascontiguousarray(vel[:, y:y + n, x:x + n]))
         assert np.array_equal(part[:, 4:-4, 4:-4], disp[:, y + 4:y + n - 4, x + 4:x + n - 4])
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2, 3])
+@pytest.mark.parametrize("at", [0, -1])
+def test_fp8_velocity_scale_at_any_alignment(C, wl, offset, at):
+    """The grid's maximum is found where it is the first or last value, at every alignment of the velocity (its scale
+    is what differs by a factor of 64 if it is not): the same bits as from an aligned copy with that maximum inside."""
+    G = 33
+    rng = np.random.default_rng(7)
+    vel = rng.uniform(-1.0, 1.0, 2 * G * G).astype(np.float32)
+    ws, bs = wl.random_weights(7)
+    W = C.Weights(ws, bs)
+    mesh = _square_mesh(C, G)
+    vel[at] = 64.0
+    buf = torch.zeros(2 * G * G + 3, dtype=torch.float32, device="cuda")
+    view = buf[offset:offset + 2 * G * G].view(2, G, G)
+    view.copy_(_dev(vel.reshape(2, G, G)))
+    got = C.predict(mesh, view, W, "fp8").cpu().numpy()
+    vel[G * G + G // 2 * G + G // 2] = 64.0  # 16 rows and columns from either corner: not in its pixel's window
+    ref = C.predict(mesh, _dev(vel.reshape(2, G, G)), W, "fp8").cpu().numpy()
+    mesh.close()
+    corner = (slice(None), slice(0, 8), slice(0, 8)) if at == 0 else (slice(None), slice(-8, None), slice(-8, None))
+    assert np.array_equal(got[corner], ref[corner])
