@@ -417,14 +417,22 @@ static __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu
         }
     };
     // conv1 of row a into its row buffer: 16-pixel blocks wave and wave + 8 of the 258 pixels, and
-    // in turn the last two pixels; zero outside the grid (conv2's padding).
+    // in turn the last two pixels; zero outside the grid (conv2's padding).  Lane group q of step st takes tap
+    // (4 st + q) mod 9: column (st + q) mod 3, and of the three velocity rows one of two that the step names (past tap 17,
+    // where the weights are zero, any pixel of the window).
     auto conv1 = [&](int a) {
         v4f* dst = s_row[a & 1];
         int ln = lane;
         asm volatile("" : "+v"(ln));  // the addresses are formed per row, not held in registers
         const int i = ln & 15, q = ln >> 4;
+        int row[3], col[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) row[k] = ((a + k - 1) & 3) * 3 * VPX;
+        col[0] = i + (q == 3 ? 0 : q);
+        col[1] = i + (q == 2 ? 0 : q == 3 ? 1 : q + 1);
+        col[2] = i + (q == 0 ? 2 : q - 1);
         auto blocks = [&](auto nblk, int mb0) {
-            constexpr int NB = decltype(nblk)::value;
+            constexpr int NB = decltype(nblk)::value;  // 1: the block of the last two pixels
             v4f acc[NB][2];
 #pragma unroll
             for (int u = 0; u < NB; ++u)
@@ -433,13 +441,12 @@ static __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
             for (int st = 0; st < 5; ++st) {
                 if (st == 3) __builtin_amdgcn_sched_barrier(0);  // not all operands at once: registers
-                int t = 4 * st + q;
-                t = t < 9 ? t : t < 18 ? t - 9 : 0;
-                const int dy = t / 3, dx = t - 3 * dy;
-                const uint32_t* src = s_vel[(a + dy - 1) & 3][0] + dx;
+                constexpr int first[5] = { 0, 1, 2, 1, 2 }, other[5] = { 1, 2, 0, 2, 0 }, lanes[5] = { 3, 2, 1, 3, 2 };
+                const uint32_t* src = s_vel[0][0] + (q < lanes[st] ? row[first[st]] : row[other[st]]);
 #pragma unroll
                 for (int u = 0; u < NB; ++u) {
-                    const uint32_t* at = src + min(16 * (mb0 + 8 * u) + i, SW + 1);
+                    const int px = 16 * (mb0 + 8 * u) + col[st % 3];
+                    const uint32_t* at = src + (NB == 1 ? min(px, VPX - 1) : px);
                     const uint32_t h = at[0];
                     const bf16x8 b = __builtin_bit_cast(bf16x8, u32x4{ h, at[VPX], at[2 * VPX], h });
 #pragma unroll
@@ -450,12 +457,13 @@ static __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu
             for (int u = 0; u < NB; ++u) {
                 const int px = 16 * (mb0 + 8 * u) + i;
                 const bool in = (unsigned)(x0 - 1 + px) < (unsigned)G && (unsigned)a < (unsigned)G;
-                if (px < SW + 2) {
+                const float top = in ? __builtin_inff() : 0.f;
+                if (NB > 1 || px < SW + 2) {
 #pragma unroll
                     for (int nb = 0; nb < 2; ++nb) {
                         v4f v = acc[u][nb];
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) v[r] = in ? fmaxf(v[r], 0.f) : 0.f;
+                        for (int r = 0; r < 4; ++r) v[r] = __builtin_amdgcn_fmed3f(v[r], 0.f, top);
                         dst[row_slot(px >> 1, px & 1, 4 * nb + q)] = v;
                     }
                 }
@@ -541,6 +549,9 @@ static __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu
     __shared__ bf16x8 s_w4[NF4 * 64];
     __shared__ float s_side[2][kWaves][4];          // a row's parts for the columns left and right of a wavefront
     __shared__ v4f s_b[2][C / 4];                   // biases of conv3 and their negatives
+    // a thread's two columns of the row completed in the previous step, without their sides (lane group q: component q)
+    __shared__ float2 s_held[kThreads];
+    __shared__ int s_from[4][kThreads];             // a thread's places in a row: float offset, or -1 outside the grid
 
     int x0, r0, r1;
     if (!block_segment(G, plan, x0, r0, r1)) return;
@@ -552,23 +563,30 @@ static __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu
 
     // act2 row a straight into its LDS buffer, 16 bytes a lane: a lane's place in LDS is given by its
     // position, so it picks the pixel and chunk that row_slot puts there; zeros outside the grid
-    // (conv3's padding).
+    // (conv3's padding).  Its pixels are the same in every row: looked up, not formed again (16 instructions each).
+    auto place = [&](int k) {
+        const int pair = k >> 4, pc = (k - 2 * pair) & 15, gx = x0 - 1 + 2 * pair + (pc >> 3);
+        return (unsigned)gx < (unsigned)G ? gx * C + 4 * (pc & 7) : -1;
+    };
+#pragma unroll
+    for (int u = 0; u < 4; ++u) s_from[u][tid] = place((wave + kWaves * u) * 64 + lane);  // read by this thread only
     auto load_row = [&](int a) {
         const float* src = act2 + (int64_t)a * G * C;
-        int ln = lane;
-        asm volatile("" : "+v"(ln));  // positions are formed per row, not held in registers
-        auto piece = [&](int p0) {
-            const int k = p0 * 64 + ln, pair = k >> 4, pc = (k - 2 * pair) & 15;
-            const int gx = x0 - 1 + 2 * pair + (pc >> 3);
-            const float* from = (unsigned)gx < (unsigned)G && (unsigned)a < (unsigned)G ? src + (int64_t)gx * C + 4 * (pc & 7)
-                                                           : reinterpret_cast<const float*>(ws + kOffZero);
-            if (k < ROWV)
-                lds_copy16(from, s_row[a & 1] + p0 * 64);
-        };
+        const float* zero = reinterpret_cast<const float*>(ws + kOffZero);
+        const bool row_in = (unsigned)a < (unsigned)G;
+        auto piece = [&](int p0, int from) { lds_copy16(row_in && from >= 0 ? src + (unsigned)from : zero, s_row[a & 1] + p0 * 64); };
         static_assert((ROWV + 63) / 64 == 4 * kWaves + 1, "four pieces per wavefront and one in turn");
 #pragma unroll
-        for (int u = 0; u < 4; ++u) piece(wave + kWaves * u);
-        if (wave == (a & 7)) piece(4 * kWaves);
+        for (int u = 0; u < 4; ++u) {
+            int ln = lane;
+            asm volatile("" : "+v"(ln));  // not all places at once: registers
+            piece(wave + kWaves * u, s_from[u][64 * wave + ln]);
+        }
+        if (wave == (a & 7)) {
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
+            if (4 * kWaves * 64 + ln < ROWV) piece(4 * kWaves, place(4 * kWaves * 64 + ln));
+        }
     };
 
     load_row(r0 - 2);
@@ -581,30 +599,30 @@ static __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu
     __syncthreads();
 
     v4f part[2][2];      // [column e][component o]: running sums for three output rows
-    float held[2][2];    // the row completed in the previous step, without its sides
 #pragma unroll
     for (int e = 0; e < 2; ++e)
 #pragma unroll
         for (int o = 0; o < 2; ++o) part[e][o] = v4f{ 0.f, 0.f, 0.f, 0.f };
 
-    // writes output row yo from `held` and the neighbouring wavefronts' parts of it
+    // writes output row yo from `held` and the neighbouring wavefronts' parts of it: lane group q < 2 component q
     auto finish = [&](int yo) {
         int ln = lane;
         asm volatile("" : "+v"(ln));
         const int i = ln & 15, q = ln >> 4;
-        const float* left = s_side[yo & 1][wave > 0 ? wave - 1 : 0];
-        const float* right = s_side[yo & 1][wave + 1 < kWaves ? wave + 1 : kWaves - 1];
+        const float left = s_side[yo & 1][wave > 0 ? wave - 1 : 0][2 + (q & 1)];
+        const float right = s_side[yo & 1][wave + 1 < kWaves ? wave + 1 : kWaves - 1][q & 1];
         const unsigned gx = x0 + WC * wave + 2 * i;
-        float* row = disp + (int64_t)yo * G;
-#pragma unroll
-        for (int o = 0; o < 2; ++o)
-            if (q == o) {
-                float d0 = held[0][o], d1 = held[1][o];
-                if (i == 0 && wave > 0) d0 += left[2 + o];
-                if (i == 15 && wave + 1 < kWaves) d1 += right[o];
-                if (gx < (unsigned)G) (row + o * GG)[gx] = d0;
-                if (gx + 1 < (unsigned)G) (row + o * GG)[gx + 1] = d1;
-            }
+        const float2 held = s_held[64 * wave + ln];
+        const float d0 = i == 0 && wave > 0 ? held.x + left : held.x;
+        const float d1 = i == 15 && wave + 1 < kWaves ? held.y + right : held.y;
+        float* to = disp + (int64_t)yo * G + gx;
+        if (q == 1) to += GG;
+        if (q < 2 && gx + 1 < (unsigned)G) {
+            to[0] = d0;
+            to[1] = d1;
+        } else if (q < 2 && gx < (unsigned)G) {
+            to[0] = d0;
+        }
     };
     RowConv rc;
     rc.u = s_u + lane;
@@ -630,13 +648,12 @@ static __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu
                     Split8 v[2];
 #pragma unroll
                     for (int e = 0; e < 2; ++e) {
+                        // columns outside the grid are conv4's zero padding
+                        const float top = x0 + WC * wave + 2 * i + e < G ? __builtin_inff() : 0.f;
 #pragma unroll
                         for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) y[e][nb][r] = fmaxf(y[e][nb][r], 0.f);
-                        // columns outside the grid are conv4's zero padding
-                        if (x0 + WC * (wave + 1) > G && x0 + WC * wave + 2 * i + e >= G)
-                            y[e][0] = y[e][1] = v4f{ 0.f, 0.f, 0.f, 0.f };
+                            for (int r = 0; r < 4; ++r) y[e][nb][r] = __builtin_amdgcn_fmed3f(y[e][nb][r], 0.f, top);
                         v[e] = split8(y[e][0], y[e][1]);
                     }
 #pragma unroll
@@ -664,21 +681,29 @@ static __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu
                 if (yo >= r0) {
                     // lane (i, q): part[e][o][2] = filter column dx = q at column 2i + e, which belongs to
                     // output column 2i + e + 1 - q
+                    float2 held;
 #pragma unroll
                     for (int o = 0; o < 2; ++o) {
                         const float z0 = part[0][o][2], z1 = part[1][o][2];
                         const float l1 = from_left(z1), r0v = from_right(z0);
-                        held[0][o] = sum_lane_column(q == 0 ? l1 : q == 1 ? z0 : q == 2 ? z1 : bias4[o]);
-                        held[1][o] = sum_lane_column(q == 0 ? z0 : q == 1 ? z1 : q == 2 ? r0v : bias4[o]);
-                        // the parts of the columns before and after the wavefront's
-                        if (i == 0 && q == 2) {
-                            s_side[yo & 1][wave][o] = z0;
-                            if (wave == 0 && strip > 0) edge[(((int64_t)(strip - 1) * 2 + 0) * G + yo) * 2 + o] = z0;
-                        }
-                        if (i == 15 && q == 0) {
-                            s_side[yo & 1][wave][2 + o] = z1;
-                            if (wave == kWaves - 1 && strip + 1 < strips)
-                                edge[(((int64_t)strip * 2 + 1) * G + yo) * 2 + o] = z1;
+                        const float d0 = sum_lane_column(q == 0 ? l1 : q == 1 ? z0 : q == 2 ? z1 : bias4[o]);
+                        const float d1 = sum_lane_column(q == 0 ? z0 : q == 1 ? z1 : q == 2 ? r0v : bias4[o]);
+                        held.x = o == 0 || q != 0 ? d0 : held.x;
+                        held.y = o == 0 || q != 0 ? d1 : held.y;
+                    }
+                    // the parts of the columns before (side 0) and after the wavefront's, in the lanes that hold them
+                    int ln = lane;
+                    asm volatile("" : "+v"(ln));
+                    s_held[64 * wave + ln] = held;
+                    if (ln == 32 || ln == 15) {
+                        const int side = ln == 32 ? 0 : 1;
+                        const float z[2] = { side ? part[1][0][2] : part[0][0][2], side ? part[1][1][2] : part[0][1][2] };
+                        s_side[yo & 1][wave][2 * side] = z[0];
+                        s_side[yo & 1][wave][2 * side + 1] = z[1];
+                        if (side ? wave == kWaves - 1 && strip + 1 < strips : wave == 0 && strip > 0) {
+                            float* to = edge + (((int64_t)(strip - 1 + side) * 2 + side) * G + yo) * 2;
+                            to[0] = z[0];
+                            to[1] = z[1];
                         }
                     }
                 }
