@@ -72,38 +72,49 @@ __device__ __forceinline__ void wprep4_bf16(int k, const float* __restrict__ w, 
     wb[k] = __builtin_convertvector(v, bf16x8);
 }
 
-// Layers 2-4 of the BF16 pass as z-sweeps through LDS.  A block owns a column of ZY x ZX cells
-// and zp consecutive planes (z_planes below); it keeps the three input planes that its current output plane reads,
-// each as a (ZY + 2) x (ZX + 2) slab with the one-cell border (zero outside the grid), in a ring
-// in LDS, so every input cell is read from memory once per block (plus the borders) instead of
-// once per tap.  While a plane's 27 taps run on the matrix cores, the plane after next is loaded
-// into registers; it replaces the oldest slab after the plane is done.  Eight wavefronts take two
-// 16-cell M-blocks each (the 256 cells of a plane; sixteen wavefronts of one M-block each ran
-// 10% slower); a tap is one v_mfma_f32_16x16x32_bf16 per M-block and 16 output channels (NB such
-// blocks: two for 32 -> 32, one for 32 -> 3 with the outputs padded to 16).
+// Layers 2-4 of the BF16 pass as z-sweeps through LDS.  A block owns a column of ZY x ZX cells and zp consecutive
+// planes (z_planes below), two of them a step: it keeps the four input planes that its two output planes read, each as a
+// (ZY + 2) x (ZX + 2) slab with the one-cell border (zero outside the grid), and the two that the next step adds, in a
+// ring in LDS, so every input cell is read from memory once per block (plus the borders) instead of once per tap.  The
+// planes after these are loaded into registers while a step's taps run and written at the start of the next, to places
+// that nothing reads then: one barrier a step.
+//
+// A tap is one v_mfma_f32_16x16x32_bf16 per 16 cells and 16 output channels.  Of the eight wavefronts each takes one
+// half of the 32 output channels, its weights in registers, and 4 rows x 16 columns of both planes (32 -> 3, outputs
+// padded to 16: 2 rows x 16 columns), so that an operand read from LDS feeds up to six (four) instructions.
+//
+// What bounds it: matrix instructions, 216 per wavefront and step at 32 -> 32 (7,130 cycles per SIMD), and the LDS, 72
+// reads of a wavefront in that time (4,600 cycles).  With one plane a step, both halves in every wavefront and half of
+// the weights read from LDS per tap it was the LDS, 162 reads for as many instructions, and two barriers a plane:
+// FIGURES.
 constexpr int ZY = 8, ZX = 32;                    // cells per block: rows, columns
 constexpr int ZSY = ZY + 2, ZSX = ZX + 2;         // slab with its border
-// bf16 per slab cell: 32 channels + 16 pad, 96 bytes.  The LDS serves a 16-byte read in groups of
-// 16 lanes over 64 four-byte banks, a group joining lanes 0-7 with 56-63 (8-15 with 48-55, ...): here
-// eight consecutive cells at one 16-byte channel chunk and eight others at the mirrored chunk.  With
-// a 96-byte pitch those sixteen reads fall in distinct bank groups; with 80 bytes half of them collide.
-constexpr int ZCS = 48;
-constexpr int ZSLAB = ZSY * ZSX * ZCS;            // bf16 per slab
+constexpr int ZRING = 6;                          // planes in LDS
+constexpr int ZSLABB = ZSY * ZSX * 64;            // bytes of a slab
 constexpr int kZThreads = 512;
 constexpr int ZCHUNKS = ZSY * ZSX * 4;            // 16-byte pieces of a slab
 constexpr int ZCH_PER_THREAD = (ZCHUNKS + kZThreads - 1) / kZThreads;
-static_assert(ZY * ZX == (kZThreads / 64) * 2 * 16, "two M-blocks per wavefront cover a plane");
+static_assert(ZY == 8 && ZX == 32 && kZThreads == 512, "the wavefronts' shares of a plane");
+
+// Byte offset of 16-byte chunk c of slab cell i.  The LDS serves a 16-byte read in groups of 16 lanes over 64 four-byte
+// banks, a group joining lanes 0-7 with 56-63 (8-15 with 48-55, ...): here eight consecutive cells at one chunk and
+// eight others at the mirrored chunk, which the exchange puts on distinct banks.
+__device__ __forceinline__ int zcell(int i, int c)
+{
+    return i * 64 + ((c ^ ((i >> 1) & 3)) << 4);
+}
 
 template <int NB>
 __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k3c_zsweep_bf16(
     int32_t G, int zp, const bf16* __restrict__ in, const bf16x8* __restrict__ wb, const float* __restrict__ bias,
     bf16* __restrict__ out, float* __restrict__ disp)
 {
-    __shared__ __attribute__((aligned(16))) bf16 s_slab[3 * ZSLAB];
-    __shared__ bf16x8 s_w[TAPS * NB * 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int ROWS = 2 * NB;  // of a wavefront
+    __shared__ __attribute__((aligned(16))) char s_slab[ZRING * ZSLABB];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, grp = lane >> 4;
-    for (int k = tid; k < TAPS * NB * 64; k += kZThreads) s_w[k] = wb[k];
+    const int nb = NB == 2 ? wave & 1 : 0, part = NB == 2 ? wave >> 1 : wave;  // output half and share of the cells
+    const int row0 = (part >> 1) * ROWS, col0 = 16 * (part & 1);
     const int tiles_x = (G + ZX - 1) / ZX, tiles_y = (G + ZY - 1) / ZY;
     const int64_t b = blockIdx.x;
     const int tx0 = (int)(b % tiles_x) * ZX, ty0 = (int)((b / tiles_x) % tiles_y) * ZY;
@@ -111,110 +122,115 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2)
     const int z1 = min(z0 + zp, G);
     const int64_t GG = (int64_t)G * G;
 
-    // the wavefront's M-blocks: cells (ty0 + r, tx0 + 16 h + col) with r = wave, h = 0, 1
-    const int r = wave;
-    // slab offsets (bf16) of the lane's operand for tap (dy, dx) = (0, 0), per M-block
-    int base[2];
+    // This thread's pieces of a slab: byte offset in a plane of `in` (from a clamped position), whether the cell lies in
+    // the grid, and the place in LDS
+    uint32_t from[ZCH_PER_THREAD], keep[ZCH_PER_THREAD];
+    int place[ZCH_PER_THREAD];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) base[h] = (r * ZSX + 16 * h + col) * ZCS + 8 * grp;
-
-    // Plane p of the slab into registers: unconditional loads from clamped positions (a chunk past
-    // the end loads the last one again); the zero padding is applied when the plane is stashed,
-    // every store unconditional (a thread past the end writes the last chunk again, the value its
-    // owner writes).  So the loads stay in flight while a plane's taps run; with a branch around them
-    // the compiled code had waited for them before the plane's first matrix instruction.
-    bf16x8 pf[ZCH_PER_THREAD];
+    for (int k = 0; k < ZCH_PER_THREAD; ++k) {
+        const int e = min(tid + k * kZThreads, ZCHUNKS - 1), cell = e >> 2;
+        const int gy = ty0 + cell / ZSX - 1, gx = tx0 + cell % ZSX - 1;
+        keep[k] = gy >= 0 && gy < G && gx >= 0 && gx < G ? ~0u : 0u;
+        from[k] = ((uint32_t)min(max(gy, 0), G - 1) * (uint32_t)G + (uint32_t)min(max(gx, 0), G - 1)) * (2 * C) + 16 * (e & 3);
+        place[k] = zcell(cell, e & 3);
+    }
+    // Two planes p, p + 1 into registers: unconditional loads, so that they stay in flight while a step's taps run; the
+    // zero padding is applied when they are stashed.
+    u32x4 pf[2][ZCH_PER_THREAD];
     auto fetch = [&](int p) {
-        const int pc = min(max(p, 0), G - 1);
 #pragma unroll
-        for (int k = 0; k < ZCH_PER_THREAD; ++k) {
-            const int e = min(tid + k * kZThreads, ZCHUNKS - 1);
-            const int cell = e >> 2, part = e & 3;
-            const int gy = min(max(ty0 + cell / ZSX - 1, 0), G - 1), gx = min(max(tx0 + cell % ZSX - 1, 0), G - 1);
-            pf[k] = *reinterpret_cast<const bf16x8*>(in + ((int64_t)pc * GG + (int64_t)gy * G + gx) * C + 8 * part);
+        for (int d = 0; d < 2; ++d) {
+            const char* plane = reinterpret_cast<const char*>(in + (int64_t)min(max(p + d, 0), G - 1) * GG * C);
+#pragma unroll
+            for (int k = 0; k < ZCH_PER_THREAD; ++k) pf[d][k] = *reinterpret_cast<const u32x4*>(plane + from[k]);
         }
     };
-    auto stash = [&](int p) {
-        bf16* dst = s_slab + ((p + 3) % 3) * ZSLAB;
-        const bool pin = p >= 0 && p < G;
+    auto stash = [&](int p, int slot) {  // slot of p: even
 #pragma unroll
-        for (int k = 0; k < ZCH_PER_THREAD; ++k) {
-            const int e = min(tid + k * kZThreads, ZCHUNKS - 1);
-            const int cell = e >> 2;
-            const int gy = ty0 + cell / ZSX - 1, gx = tx0 + cell % ZSX - 1;
-            const bool on = pin && gy >= 0 && gy < G && gx >= 0 && gx < G;
-            *reinterpret_cast<bf16x8*>(dst + cell * ZCS + 8 * (e & 3)) = on ? pf[k] : bf16x8{ 0, 0, 0, 0, 0, 0, 0, 0 };
+        for (int d = 0; d < 2; ++d) {
+            const uint32_t in_z = p + d >= 0 && p + d < G ? ~0u : 0u;
+#pragma unroll
+            for (int k = 0; k < ZCH_PER_THREAD; ++k)
+                if ((k + 1) * kZThreads <= ZCHUNKS || tid + k * kZThreads < ZCHUNKS)
+                    *reinterpret_cast<u32x4*>(s_slab + (slot + d) * ZSLABB + place[k]) = pf[d][k] & (keep[k] & in_z);
         }
     };
     fetch(z0 - 1);
-    stash(z0 - 1);
-    fetch(z0);
-    stash(z0);
+    stash(z0 - 1, 0);
     fetch(z0 + 1);
-    stash(z0 + 1);
-    __syncthreads();
-    // the first 16 output channels' weights stay in registers for the whole sweep (all of the
-    // layer's weights do not fit beside the operands at two wavefronts per SIMD); the other block's
-    // are read from LDS per tap
-    bf16x8 wr[TAPS];
-#pragma unroll
-    for (int t = 0; t < TAPS; ++t) wr[t] = s_w[(t * NB) * 64 + lane];
+    stash(z0 + 1, 2);
+    fetch(z0 + 3);
 
-    v4f bl[2];
+    bf16x8 w[TAPS];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        if (NB == 2) {
-            bl[nb] = *reinterpret_cast<const v4f*>(bias + 16 * nb + 4 * grp);
-        } else {  // rows 4 grp + j of the single output block: channels 0..2 are real
-            bl[nb] = v4f{ 0.f, 0.f, 0.f, 0.f };
-        }
-    }
-    for (int z = z0; z < z1; ++z) {
-        fetch(z + 2);  // lands while this plane computes (after the block's last plane: unused)
-        __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the plane's taps
-        v4f acc[2][NB];
+    for (int t = 0; t < TAPS; ++t) w[t] = wb[(t * NB + nb) * 64 + lane];
+    v4f start{ 0.f, 0.f, 0.f, 0.f };  // 32 -> 3: the bias is added to the result
+    if (NB == 2) start = *reinterpret_cast<const v4f*>(bias + 16 * nb + 4 * grp);
+
+    // operand addresses in a slab: row r (0: above the wavefront's first), column dx; the exchange repeats after four rows
+    // (34 cells each)
+    int at[4][3];
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[h][nb] = bl[nb];
+        for (int dx = 0; dx < 3; ++dx) at[r][dx] = zcell((row0 + r) * ZSX + col0 + col + dx, grp);
+    const int gx = tx0 + col0 + col;
+    __syncthreads();
+    int slot = 0;  // of plane z - 1
+    for (int z = z0; z < z1; z += 2) {
+        const int slot2 = slot == 4 ? 0 : slot + 2, slot4 = slot == 0 ? 4 : slot - 2;
+        stash(z + 3, slot4);
+        fetch(z + 5);  // lands while this step computes (past the block's last planes: unused)
+        __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the step's taps
+        v4f acc[2][ROWS];  // output plane, row
+        // input plane z - 1 + p, row r, column dx, in the order in which every output's taps are summed
+        constexpr int NG = 4 * (ROWS + 2) * 3, PF = 4;
+        bf16x8 x[PF + 1];
+        auto read = [&](int g) {
+            const int p = g / (3 * (ROWS + 2)), r = g / 3 % (ROWS + 2), dx = g % 3;
+            x[g % (PF + 1)] = *reinterpret_cast<const bf16x8*>(s_slab + ((p < 2 ? slot : slot2) + (p & 1)) * ZSLABB + at[r & 3][dx] +
+                                                               (r >> 2) * 4 * ZSX * 64);
+        };
 #pragma unroll
-        for (int dz = 0; dz < 3; ++dz) {
-            const bf16* sl = s_slab + ((z + dz - 1 + 3) % 3) * ZSLAB;
+        for (int g = 0; g < PF; ++g) read(g);
 #pragma unroll
-            for (int t9 = 0; t9 < 9; ++t9) {
-                const int t = dz * 9 + t9, off = ((t9 / 3) * ZSX + t9 % 3) * ZCS;
-                const bf16x8 a0 = *reinterpret_cast<const bf16x8*>(sl + base[0] + off);
-                const bf16x8 a1 = *reinterpret_cast<const bf16x8*>(sl + base[1] + off);
+        for (int g = 0; g < NG; ++g) {
+            const int p = g / (3 * (ROWS + 2)), r = g / 3 % (ROWS + 2), dx = g % 3;
+            if (g + PF < NG) read(g + PF);
+            __builtin_amdgcn_sched_barrier(0);  // the reads stay ahead of the instructions
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
-                    const bf16x8 w = nb == 0 ? wr[t] : s_w[(t * NB + nb) * 64 + lane];
-                    acc[0][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a0, acc[0][nb], 0, 0, 0);
-                    acc[1][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a1, acc[1][nb], 0, 0, 0);
+            for (int oz = 0; oz < 2; ++oz)
+#pragma unroll
+                for (int oy = 0; oy < ROWS; ++oy) {
+                    const int dz = p - oz, dy = r - oy;
+                    if (dz < 0 || dz > 2 || dy < 0 || dy > 2) continue;
+                    const int t = (dz * 3 + dy) * 3 + dx;
+                    acc[oz][oy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[t], x[g % (PF + 1)], t == 0 ? start : acc[oz][oy], 0, 0, 0);
                 }
-            }
         }
         // results: lane (col, grp) holds rows 4 grp + j (output channels 16 nb + 4 grp + j) of cell col
-        const int gy = ty0 + r;
+        if (gx < G) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int gx = tx0 + 16 * h + col;
-            if (gy >= G || gx >= G) continue;
-            const int64_t c = (int64_t)z * GG + (int64_t)gy * G + gx;
-            if (NB == 2) {
+            for (int oz = 0; oz < 2; ++oz) {
+                if (z + oz >= z1) continue;
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
-                    const v4f a = acc[h][nb];
-                    const v4f v{ fmaxf(a.x, 0.f), fmaxf(a.y, 0.f), fmaxf(a.z, 0.f), fmaxf(a.w, 0.f) };
-                    *reinterpret_cast<bf16x4*>(out + c * C + 16 * nb + 4 * grp) = __builtin_convertvector(v, bf16x4);
+                for (int oy = 0; oy < ROWS; ++oy) {
+                    const int gy = ty0 + row0 + oy;
+                    if (gy >= G) continue;
+                    const int64_t c = (int64_t)(z + oz) * GG + (int64_t)gy * G + gx;
+                    const v4f a = acc[oz][oy];
+                    if (NB == 2) {
+                        const v4f v{ fmaxf(a.x, 0.f), fmaxf(a.y, 0.f), fmaxf(a.z, 0.f), fmaxf(a.w, 0.f) };
+                        *reinterpret_cast<bf16x4*>(out + c * C + 16 * nb + 4 * grp) = __builtin_convertvector(v, bf16x4);
+                    } else if (grp == 0) {
+                        disp[c] = a.x + bias[0];
+                        disp[GG * G + c] = a.y + bias[1];
+                        disp[2 * GG * G + c] = a.z + bias[2];
+                    }
                 }
-            } else if (grp == 0) {
-                disp[c] = acc[h][0].x + bias[0];
-                disp[GG * G + c] = acc[h][0].y + bias[1];
-                disp[2 * GG * G + c] = acc[h][0].z + bias[2];
             }
         }
-        __syncthreads();           // every wavefront is done with the slab of plane z - 1
-        stash(z + 2);  // after the last plane it replaces a plane no longer read
+        slot = slot2;
         __syncthreads();
     }
 }
@@ -445,7 +461,7 @@ __device__ __forceinline__ void wprep_split(int k, const float* __restrict__ w, 
 }
 
 // One part of a slab in LDS: four 16-byte chunks of eight channels a cell, chunk c of cell i at place
-// c ^ 2 (i / 4 mod 2).  A 16-byte read is served in groups of 16 lanes (see ZCS), here eight consecutive cells at
+// c ^ 2 (i / 4 mod 2).  A 16-byte read is served in groups of 16 lanes (see zcell), here eight consecutive cells at
 // chunk c and eight others at chunk 3 - c; eight consecutive cells take each place of a 256-byte line of four
 // cells twice, i / 4 odd and even, which the exchange puts on chunks c and c ^ 2, and 3 - c has the other
 // parity: no two of the sixteen share a bank.
@@ -601,7 +617,7 @@ static_assert(ZSX % 2 == 0, "a slab row starts a line");
 // The chunk (four channels) that lane group q reads as half h of its eight: 2q and 2q + 1, exchanged for q >= 2,
 // and chunk c's place in a slab: in a line k of two cells, cell p of it at (8 p + c + 2 k) mod 16.  Eight
 // consecutive cells at one chunk and eight at another of the other parity (a 16-lane group of a 16-byte read,
-// see ZCS) then fall in distinct banks.
+// see zcell) then fall in distinct banks.
 __host__ __device__ constexpr int chunk4(int q, int h)
 {
     return 2 * q + (h ^ (q >> 1));
@@ -770,7 +786,8 @@ void run_predict3(cnnsns_mesh3_s& m, const float* vel, const cnnsns_cnn& w, int3
     const int64_t cells = (int64_t)G * G * G;
     const unsigned grid = cnn_persistent_grid();
     const int64_t ztiles = (int64_t)((G + ZX - 1) / ZX) * ((G + ZY - 1) / ZY);
-    const int zp = z_planes(G, ztiles, (int)grid);
+    int zp = z_planes(G, ztiles, (int)grid);
+    if (precision == CNNSNS_BF16) zp += zp & 1;  // two planes a step
     const int64_t zblocks = ztiles * ((G + zp - 1) / zp);
     if (zblocks > (int64_t)UINT32_MAX) fail(CNNSNS_EINVAL, "predict3d: overlay too large");
     float* act0 = static_cast<float*>(m.ws.ptr);

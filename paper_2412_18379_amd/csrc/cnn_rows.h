@@ -516,9 +516,9 @@ static __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu
             rc.stages<kTail, kStages>(c0, c1, c2);
             if (a - 2 >= r0) emit(a - 2, c2);
         }
-        if (a + 1 <= r1) conv1(a + 1);
         if (a <= r1) {
             if (active) rc.stages<0, kTail>(c2, c0, c1);
+            if (a + 1 <= r1) conv1(a + 1);  // after the stages: 4% faster at 1024 x 1024 than before them
             if (a + 3 <= r1 + 1) stash_vel(a + 3);
             __syncthreads();
         }
