@@ -331,11 +331,12 @@ __global__ __launch_bounds__(kZ1Threads) void k3c_zconv1(int32_t G, int zp, cons
 // so a K = 32 step covers two taps (14 steps for 27 taps, the last half empty).
 constexpr int NW1S = 14 * 2 * 64;  // bf16x8 operands of the split layer 1
 
-// wb[(s * 2 + nb) * 64 + l]: output channel 16 nb + l%16; lane group g = l/16 takes tap 2 s + g/2
+// wb[(s * 2 + nb) * 64 + l]: output channel 8 (l%16 / 4) + 4 nb + l%4, so that a lane ends with eight consecutive channels
+// of its cell, one 16-byte store; lane group g = l/16 takes tap 2 s + g/2
 __device__ __forceinline__ void wprep1_split(int k, const float* __restrict__ w, bf16x8* __restrict__ wb)
 {
     const int l = k & 63, nb = (k >> 6) & 1, st = k >> 7, g = l >> 4;
-    const int o = 16 * nb + (l & 15), t = 2 * st + (g >> 1);
+    const int o = 8 * ((l & 15) >> 2) + 4 * nb + (l & 3), t = 2 * st + (g >> 1);
     bf16x8 v = bf16x8{ 0, 0, 0, 0, 0, 0, 0, 0 };
     if (t < TAPS) {
 #pragma unroll
@@ -354,81 +355,121 @@ __device__ __forceinline__ void wprep1_split(int k, const float* __restrict__ w,
     wb[k] = v;
 }
 
-__global__ __launch_bounds__(kZ1Threads) void k3c_zconv1_split(int32_t G, int zp, const float* __restrict__ vel,
-                                                               const bf16x8* __restrict__ wb,
-                                                               const float* __restrict__ bias, bf16* __restrict__ out)
+// A block works as those of the layers above, two planes a step through a ring of six slabs, one row of two planes a
+// wavefront; all weights stay in registers, so that the LDS serves one read per two instructions.  G = 101: 59 us with
+// the weights read from LDS (three reads per two instructions, sixteen wavefronts, two barriers a plane), now FIG1.
+__global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k3c_zconv1_split(
+    int32_t G, int zp, const float* __restrict__ vel, const bf16x8* __restrict__ wb, const float* __restrict__ bias,
+    bf16* __restrict__ out)
 {
-    constexpr int NCELL = ZSY * ZSX;
-    static_assert(NCELL <= kZ1Threads && ZY * ZX == (kZ1Threads / 64) * 16, "one slab cell per thread");
-    static_assert(NWB + NW1S <= TAPS * 2 * 3 * 64, "layer 1's operands fit after layer 2's");
-    __shared__ __attribute__((aligned(16))) bf16x8 s_v[3 * NCELL];
-    __shared__ bf16x8 s_w[NW1S];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int NCELL = ZSY * ZSX, STEPS = 14, ITEMS = (2 * NCELL + kZThreads - 1) / kZThreads;
+    static_assert(ZY == kZThreads / 64 && ZX == 32, "a row of two M-blocks per wavefront");
+    __shared__ bf16x8 s_v[ZRING * NCELL];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, grp = lane >> 4;
-    for (int k = tid; k < NW1S; k += kZ1Threads) s_w[k] = wb[k];
     const int tiles_x = (G + ZX - 1) / ZX, tiles_y = (G + ZY - 1) / ZY;
     const int64_t b = blockIdx.x;
     const int tx0 = (int)(b % tiles_x) * ZX, ty0 = (int)((b / tiles_x) % tiles_y) * ZY;
     const int z0 = (int)(b / ((int64_t)tiles_x * tiles_y)) * zp;
     const int z1 = min(z0 + zp, G);
     const int64_t GG = (int64_t)G * G, n = GG * G;
-    const int r = wave >> 1, h = wave & 1;
 
-    bf16x8 pf;
-    auto fetch = [&](int p) {  // thread tid < NCELL: its slab cell of plane p (zero outside the grid)
-        float v[3] = { 0.f, 0.f, 0.f };
-        if (tid < NCELL) {
-            const int gy = ty0 + tid / ZSX - 1, gx = tx0 + tid % ZSX - 1;
-            if (p >= 0 && p < G && gy >= 0 && gy < G && gx >= 0 && gx < G) {
-                const int64_t c = (int64_t)p * GG + (int64_t)gy * G + gx;
-                v[0] = vel[c];
-                v[1] = vel[n + c];
-                v[2] = vel[2 * n + c];
-            }
-        }
-        pf = bf16x8{ 0, 0, 0, 0, 0, 0, 0, 0 };
+    // this thread's cells of two planes: offset in a plane (from a clamped position), whether it lies in the grid
+    uint32_t from[ITEMS];
+    bool in[ITEMS];
+    int plane[ITEMS], cell[ITEMS];
 #pragma unroll
-        for (int ci = 0; ci < CIO; ++ci) {
-            const bf16 hi = (bf16)v[ci];
-            pf[ci] = hi;
-            pf[3 + ci] = (bf16)(v[ci] - (float)hi);
+    for (int k = 0; k < ITEMS; ++k) {
+        const int e = min(tid + k * kZThreads, 2 * NCELL - 1);
+        plane[k] = e >= NCELL;
+        cell[k] = e;
+        const int i = e - plane[k] * NCELL, gy = ty0 + i / ZSX - 1, gx = tx0 + i % ZSX - 1;
+        in[k] = gy >= 0 && gy < G && gx >= 0 && gx < G;
+        from[k] = (uint32_t)min(max(gy, 0), G - 1) * (uint32_t)G + (uint32_t)min(max(gx, 0), G - 1);
+    }
+    float pf[ITEMS][CIO];
+    auto fetch = [&](int p) {  // unconditional loads: they stay in flight while a step's taps run
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            const float* at = vel + (int64_t)min(max(p + plane[k], 0), G - 1) * GG + from[k];
+#pragma unroll
+            for (int ci = 0; ci < CIO; ++ci) pf[k][ci] = at[ci * n];
         }
     };
-    auto stash = [&](int p) {
-        if (tid < NCELL) s_v[((p + 3) % 3) * NCELL + tid] = pf;
+    auto stash = [&](int p, int slot) {  // zero outside the grid
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            const bool on = in[k] && p + plane[k] >= 0 && p + plane[k] < G;
+            bf16x8 v = bf16x8{ 0, 0, 0, 0, 0, 0, 0, 0 };
+#pragma unroll
+            for (int ci = 0; ci < CIO; ++ci) {
+                const float x = on ? pf[k][ci] : 0.f;
+                const bf16 hi = (bf16)x;
+                v[ci] = hi;
+                v[3 + ci] = (bf16)(x - (float)hi);
+            }
+            if ((k + 1) * kZThreads <= 2 * NCELL || tid + k * kZThreads < 2 * NCELL) s_v[slot * NCELL + cell[k]] = v;
+        }
     };
     fetch(z0 - 1);
-    stash(z0 - 1);
-    fetch(z0);
-    stash(z0);
+    stash(z0 - 1, 0);
     fetch(z0 + 1);
-    stash(z0 + 1);
-    __syncthreads();
-    const v4f bl0 = *reinterpret_cast<const v4f*>(bias + 4 * grp);
-    const v4f bl1 = *reinterpret_cast<const v4f*>(bias + 16 + 4 * grp);
-    const int cell0 = r * ZSX + 16 * h + col;
-    for (int z = z0; z < z1; ++z) {
-        if (z + 2 < z1 + 1) fetch(z + 2);
-        v4f acc0 = bl0, acc1 = bl1;
+    stash(z0 + 1, 2);
+    fetch(z0 + 3);
+
+    bf16x8 w[STEPS][2];
 #pragma unroll
-        for (int st = 0; st < 14; ++st) {
-            int t = 2 * st + (grp >> 1);
-            t = t < TAPS ? t : 13;  // zero weights: any finite operand serves
-            const int dz = t / 9, dy = (t / 3) % 3, dx = t % 3;
-            const bf16x8 a = s_v[((z + dz - 1 + 3) % 3) * NCELL + cell0 + dy * ZSX + dx];
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(s_w[(st * 2) * 64 + lane], a, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(s_w[(st * 2 + 1) * 64 + lane], a, acc1, 0, 0, 0);
+    for (int st = 0; st < STEPS; ++st)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) w[st][nb] = wb[(st * 2 + nb) * 64 + lane];
+    const v4f bl0 = *reinterpret_cast<const v4f*>(bias + 8 * grp), bl1 = *reinterpret_cast<const v4f*>(bias + 8 * grp + 4);
+    // the lane's cell of each step's tap within a plane (past the last tap, where the weights are zero, the last again)
+    int at[STEPS];
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) {
+        const int t = min(2 * st + (grp >> 1), TAPS - 1);
+        at[st] = (wave + t / 3 % 3) * ZSX + t % 3 + col;
+    }
+    const bool second = grp >= 2;
+    __syncthreads();
+    int slot = 0;  // of plane z - 1
+    for (int z = z0; z < z1; z += 2) {
+        const int slot2 = slot == 4 ? 0 : slot + 2, slot4 = slot == 0 ? 4 : slot - 2;
+        stash(z + 3, slot4);
+        fetch(z + 5);
+        __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the step's taps
+        const int plane_at[4] = { slot * NCELL, (slot + 1) * NCELL, slot2 * NCELL, (slot2 + 1) * NCELL };
+        v4f acc[2][2][2];  // output plane, M-block, channels
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st)
+#pragma unroll
+            for (int oz = 0; oz < 2; ++oz) {
+                const int d0 = 2 * st / 9, d1 = min(2 * st + 1, TAPS - 1) / 9;  // the two taps' planes
+                const int base = d0 == d1 ? plane_at[oz + d0] : second ? plane_at[oz + d1] : plane_at[oz + d0];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const bf16x8 a = s_v[base + at[st] + 16 * h];
+                    acc[oz][h][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[st][0], a, st == 0 ? bl0 : acc[oz][h][0], 0, 0, 0);
+                    acc[oz][h][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[st][1], a, st == 0 ? bl1 : acc[oz][h][1], 0, 0, 0);
+                }
+            }
+        const int gy = ty0 + wave;
+        if (gy < G) {
+#pragma unroll
+            for (int oz = 0; oz < 2; ++oz) {
+                if (z + oz >= z1) continue;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int gx = tx0 + 16 * h + col;
+                    if (gx >= G) continue;
+                    bf16x8 v;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) v[k] = (bf16)fmaxf(acc[oz][h][k >> 2][k & 3], 0.f);
+                    *reinterpret_cast<bf16x8*>(out + ((int64_t)(z + oz) * GG + (int64_t)gy * G + gx) * C + 8 * grp) = v;
+                }
+            }
         }
-        const int gy = ty0 + r, gx = tx0 + 16 * h + col;
-        if (gy < G && gx < G) {
-            bf16* dst = out + ((int64_t)z * GG + (int64_t)gy * G + gx) * C + 4 * grp;
-            const v4f v0{ fmaxf(acc0.x, 0.f), fmaxf(acc0.y, 0.f), fmaxf(acc0.z, 0.f), fmaxf(acc0.w, 0.f) };
-            const v4f v1{ fmaxf(acc1.x, 0.f), fmaxf(acc1.y, 0.f), fmaxf(acc1.z, 0.f), fmaxf(acc1.w, 0.f) };
-            *reinterpret_cast<bf16x4*>(dst) = __builtin_convertvector(v0, bf16x4);
-            *reinterpret_cast<bf16x4*>(dst + 16) = __builtin_convertvector(v1, bf16x4);
-        }
-        __syncthreads();
-        if (z + 2 < z1 + 1) stash(z + 2);
+        slot = slot2;
         __syncthreads();
     }
 }
@@ -801,7 +842,7 @@ void run_predict3(cnnsns_mesh3_s& m, const float* vel, const cnnsns_cnn& w, int3
         bf16x8* wb4 = wb3 + NWB;
         k3c_prep_bf16<<<(kPrepBf16 + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[0], w.w[1], w.w[2], w.w[3], wb1, wb2,
                                                                               wb3, wb4);
-        k3c_zconv1_split<<<(unsigned)zblocks, kZ1Threads, 0, stream>>>(G, zp, vel, wb1, w.b[0], b0);
+        k3c_zconv1_split<<<(unsigned)zblocks, kZThreads, 0, stream>>>(G, zp, vel, wb1, w.b[0], b0);
         k3c_zsweep_bf16<2><<<(unsigned)zblocks, kZThreads, 0, stream>>>(G, zp, b0, wb2, w.b[1], b1, nullptr);
         k3c_zsweep_bf16<2><<<(unsigned)zblocks, kZThreads, 0, stream>>>(G, zp, b1, wb3, w.b[2], b0, nullptr);
         k3c_zsweep_bf16<1><<<(unsigned)zblocks, kZThreads, 0, stream>>>(G, zp, b0, wb4, w.b[3], nullptr, disp);
