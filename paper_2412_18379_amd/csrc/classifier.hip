@@ -335,12 +335,13 @@ __global__ __launch_bounds__(kMThreads) __attribute__((amdgpu_waves_per_eu(3, 3)
 // instruction with both operands as three BF16 values (split.h).  A block takes BM particles x BN outputs; a
 // wavefront MB x NB blocks of 16 x 16 (rows = outputs, columns = particles, so a lane ends with four consecutive
 // outputs of a particle), the products of the high parts and the small ones in accumulators of their
-// own.  K goes in slices of 32, double-buffered in LDS: the weights' operands are copied straight into LDS as
-// prepared (k_cls_prep), the activations are loaded into registers, split and written after the slice's products.
+// own.  K goes in slices of 32, KS of them a step, double-buffered in LDS: the weights' operands are copied straight
+// into LDS as prepared (k_cls_prep), the activations are loaded into registers, split and written after the step's
+// products.  Small tiles, whose steps are latency and not products, take two slices a step.
 //
 // What bounds it: matrix instructions, 96 per wavefront and slice (16.5 cycles each) at 128 x 256, 1.5 us of the
-// 3.2 a slice takes; the rest is the splitting, the LDS reads and the barrier, which one block per compute unit
-// does not hide.  65,536 particles, 512 -> 512: 0.21 ms, 0.36 on the FP32 instruction in 128 x 128 tiles.  One kernel
+// 2.8 a slice takes; the rest is the splitting, the LDS reads and the barrier, which one block per compute unit
+// does not hide.  65,536 particles, 512 -> 512: 0.18 ms, 0.36 on the FP32 instruction in 128 x 128 tiles.  One kernel
 // for all three layers with the activations passed on already split took 0.30 ms against 0.31 for the three, and
 // 69 us against 46 at 300 particles, where a block's serial chain of slices is all that counts.
 constexpr int kDenseThreads = 512;
@@ -382,7 +383,7 @@ __device__ __forceinline__ int dense_slot(int r, int c)
 }
 
 // N outputs, of which n_real exist (rows of C hold ldc; with VEC all exist and a lane's four are stored at once)
-template <int MB, int NB, int WM, int WN, bool RELU, bool VEC>
+template <int MB, int NB, int WM, int WN, int KS, bool RELU, bool VEC>
 __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_dense_split(
     int M, int N, int n_real, int K, const float* __restrict__ A, int lda, const bf16x8* __restrict__ ws,
     const float* __restrict__ bias, float* __restrict__ Cm, int ldc)
@@ -391,43 +392,52 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
     constexpr int BM = 16 * MB * WM, BN = 16 * NB * WN, NF = BN / 16 * 3;  // weight operands of a slice
     constexpr int PER = BM * 8 / kDenseThreads;
     static_assert(BM * 8 % kDenseThreads == 0, "whole rounds of activation loads");
-    __shared__ bf16x8 s_w[2][NF * 64];
-    __shared__ bf16x8 s_x[2][3 * BM * 4];
+    __shared__ bf16x8 s_w[2][KS][NF * 64];
+    __shared__ bf16x8 s_x[2][KS][3 * BM * 4];
     const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
     const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
 
-    // weights of slice ks straight into LDS, one operand (64 lanes x 16 bytes) a wavefront instruction
+    // weights of step ks (KS slices) straight into LDS, one operand (64 lanes x 16 bytes) a wavefront instruction
     auto load_w = [&](int ks) {
-        const bf16x8* src = ws + ((int64_t)ks * (N / 16) + n0 / 16) * 192 + lane;
-        for (int f = wave; f < NF; f += 8)
-            lds_copy16(src + f * 64, s_w[ks & 1] + f * 64);
+        const bf16x8* src = ws + ((int64_t)ks * KS * (N / 16) + n0 / 16) * 192 + lane;
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int k = 0; k < (NF + 7) / 8; ++k) {  // no loop: a taken branch costs some 40 cycles
+                const int f = wave + 8 * k;
+                if (8 * (k + 1) <= NF || f < NF) lds_copy16(src + s * (N / 16) * 192 + f * 64, s_w[ks & 1][s] + f * 64);
+            }
     };
-    v4f pa[PER];
+    v4f pa[KS][PER];
     auto fetch = [&](int ks) {
 #pragma unroll
-        for (int h = 0; h < PER; ++h) {
-            const int e = tid + h * kDenseThreads, r = min(m0 + (e >> 3), M - 1);  // rows past M: not stored
-            pa[h] = *reinterpret_cast<const v4f*>(A + (int64_t)r * lda + 32 * ks + 4 * (e & 7));
-        }
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int h = 0; h < PER; ++h) {
+                const int e = tid + h * kDenseThreads, r = min(m0 + (e >> 3), M - 1);  // rows past M: not stored
+                pa[s][h] = *reinterpret_cast<const v4f*>(A + (int64_t)r * lda + 32 * (ks * KS + s) + 4 * (e & 7));
+            }
     };
     auto stash = [&](int ks) {
 #pragma unroll
-        for (int h = 0; h < PER; ++h) {
-            const int e = tid + h * kDenseThreads;
-            u32x2 p[3];
-            uint32_t a, b, c;
+        for (int s = 0; s < KS; ++s)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                split_pair(pa[h][2 * j], pa[h][2 * j + 1], a, b, c);
-                p[0][j] = a;
-                p[1][j] = b;
-                p[2][j] = c;
+            for (int h = 0; h < PER; ++h) {
+                const int e = tid + h * kDenseThreads;
+                u32x2 p[3];
+                uint32_t a, b, c;
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    split_pair(pa[s][h][2 * j], pa[s][h][2 * j + 1], a, b, c);
+                    p[0][j] = a;
+                    p[1][j] = b;
+                    p[2][j] = c;
+                }
+                u32x2* to = reinterpret_cast<u32x2*>(s_x[ks & 1][s] + dense_slot(e >> 3, (e & 7) >> 1)) + (e & 1);
+#pragma unroll
+                for (int part = 0; part < 3; ++part) to[part * BM * 8] = p[part];
             }
-            u32x2* to = reinterpret_cast<u32x2*>(s_x[ks & 1] + dense_slot(e >> 3, (e & 7) >> 1)) + (e & 1);
-#pragma unroll
-            for (int part = 0; part < 3; ++part) to[part * BM * 8] = p[part];
-        }
     };
     v4f hi[MB][NB], lo[MB][NB];
 #pragma unroll
@@ -449,36 +459,45 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
     stash(0);
     lds_copies_arrived();  // the weights have arrived
     __syncthreads();
-    const int slices = K / 32;
-    for (int ks = 0; ks < slices; ++ks) {
-        if (ks + 1 < slices) {  // lands while this slice's products issue
-            load_w(ks + 1);
-            fetch(ks + 1);
+    const int steps = K / (32 * KS);
+    auto products = [&](int ks) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const bf16x8* sw = s_w[ks & 1][s] + wn * NB * 192 + lane;
+            const bf16x8* sx = s_x[ks & 1][s];
+            bf16x8 w[NB][3], x[MB][3];
+#pragma unroll
+            for (int part = 0; part < 3; ++part) {
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) w[nb][part] = sw[(nb * 3 + part) * 64];
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) x[mb][part] = sx[part * BM * 4 + dense_slot(16 * (wm * MB + mb) + i, q)];
+            }
+            constexpr int wp[6] = { 0, 0, 1, 1, 0, 2 }, xp[6] = { 0, 1, 0, 1, 2, 0 };
+#pragma unroll
+            for (int k = 0; k < 6; ++k)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        v4f& acc = k == 0 ? hi[mb][nb] : lo[mb][nb];
+                        acc = mfma_bf16(w[nb][wp[k]], x[mb][xp[k]], acc);
+                    }
         }
-        const bf16x8* sw = s_w[ks & 1] + wn * NB * 192 + lane;
-        const bf16x8* sx = s_x[ks & 1];
-        bf16x8 w[NB][3], x[MB][3];
-#pragma unroll
-        for (int part = 0; part < 3; ++part) {
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) w[nb][part] = sw[(nb * 3 + part) * 64];
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) x[mb][part] = sx[part * BM * 4 + dense_slot(16 * (wm * MB + mb) + i, q)];
-        }
-        constexpr int wp[6] = { 0, 0, 1, 1, 0, 2 }, xp[6] = { 0, 1, 0, 1, 2, 0 };
-#pragma unroll
-        for (int k = 0; k < 6; ++k)
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
-                    v4f& acc = k == 0 ? hi[mb][nb] : lo[mb][nb];
-                    acc = mfma_bf16(w[nb][wp[k]], x[mb][xp[k]], acc);
-                }
-        if (ks + 1 < slices) stash(ks + 1);
+    };
+    // The last step apart, so that no load is pending where the loop starts again: the compiler would wait for it
+    // there, and with it for the copies just issued.
+    for (int ks = 0; ks + 1 < steps; ++ks) {
+        load_w(ks + 1);  // these land while the step's products issue
+        fetch(ks + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        products(ks);
+        if (KS > 1) __builtin_amdgcn_sched_barrier(0);  // few products: none wait for the activations
+        stash(ks + 1);
         lds_copies_arrived();
         __syncthreads();
     }
+    products(steps - 1);
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
         const int m = m0 + 16 * (wm * MB + mb) + i;
@@ -502,8 +521,8 @@ __global__ __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(2
 }
 
 // The layer on M particles: 128 x 256 tiles while they fill the chip, 128 x 64 tiles for a last round that would
-// leave most compute units idle.  A round of the large tiles takes 51 us (512 -> 512), one of the small ones, four
-// times as many blocks, 16: the small ones are the faster up to three rounds.
+// leave most compute units idle.  A round of the large tiles takes 45 us (512 -> 512), one of the small ones, four
+// times as many blocks, 14: the small ones are the faster up to three rounds.
 template <bool RELU>
 void dense(int M, int N, int K, const float* A, int lda, const bf16x8* ws, const float* bias, float* Cm, int ldc,
            unsigned cus, hipStream_t stream)
@@ -513,10 +532,25 @@ void dense(int M, int N, int K, const float* A, int lda, const bf16x8* ws, const
     if ((mt - large) * 4 * nb > 3 * cus) large = mt;
     const int rows = (int)std::min<unsigned>(large * 128, (unsigned)M);
     if (large)
-        k_dense_split<4, 4, 2, 4, RELU, true><<<dim3(large, nb), kDenseThreads, 0, stream>>>(rows, N, N, K, A, lda, ws, bias, Cm, ldc);
+        k_dense_split<4, 4, 2, 4, 1, RELU, true><<<dim3(large, nb), kDenseThreads, 0, stream>>>(rows, N, N, K, A, lda, ws, bias, Cm, ldc);
     if (large < mt)
-        k_dense_split<2, 2, 4, 2, RELU, true><<<dim3(mt - large, N / 64), kDenseThreads, 0, stream>>>(
+        k_dense_split<2, 2, 4, 2, 2, RELU, true><<<dim3(mt - large, N / 64), kDenseThreads, 0, stream>>>(
             M - rows, N, N, K, A + (int64_t)rows * lda, lda, ws, bias, Cm + (int64_t)rows * ldc, ldc);
+}
+
+// The last layer, 512 -> 81, in the same way: 128-row blocks in whole rounds, and 64-row blocks, two slices a step, for a
+// last round that these cover at once (300 particles: 12 us against 20 with 128 rows; 65,536: 62 against 57).
+void dense_logits(int M, const float* A, const bf16x8* ws, const float* bias, float* L, unsigned cus, hipStream_t stream)
+{
+    const unsigned mt = (unsigned)((M + 127) / 128);
+    unsigned large = mt - mt % cus;
+    if ((mt - large) * 2 > cus) large = mt;
+    const int rows = (int)std::min<unsigned>(large * 128, (unsigned)M), rest = M - rows;
+    if (large)
+        k_dense_split<2, 3, 4, 2, 1, false, false><<<large, kDenseThreads, 0, stream>>>(rows, kNL, kNA, kH2, A, kH2, ws, bias, L, kNA);
+    if (rest)
+        k_dense_split<1, 3, 4, 2, 2, false, false><<<(rest + 63) / 64, kDenseThreads, 0, stream>>>(
+            rest, kNL, kNA, kH2, A + (int64_t)rows * kH2, kH2, ws, bias, L + (int64_t)rows * kNA, kNA);
 }
 
 // The argmax of each particle's logits (the lowest class on ties) and its start element: the lookup element
@@ -639,8 +673,7 @@ void run_classify(cnnsns_mesh_s& m, int64_t n, const double* xp, const cnnsns_cl
             Z, kNZ, Hb, kH2);
         dense<true>(mc, kH1, kH1, Hb, kH2, wd, w.b[3], Z + kNF, kNZ, cus, stream);
         dense<true>(mc, kH2, kNZ, Z, kNZ, wd + kD1, w.b[4], Hb, kH2, cus, stream);
-        k_dense_split<2, 3, 4, 2, false, false><<<dim3((mc + 127) / 128, 1), kDenseThreads, 0, stream>>>(
-            mc, kNL, kNA, kH2, Hb, kH2, wd + kD1 + kD2, w.b[5], L, kNA);
+        dense_logits(mc, Hb, wd + kD1 + kD2, w.b[5], L, cus, stream);
         k_cls_argmax<<<blocks_for(mc, kBlock), kBlock, 0, stream>>>(mc, xp2 + c0, m.G, m.lookup, L, kNA,
                                                                     fallback ? fallback + c0 : nullptr, start + c0,
                                                                     cls ? cls + c0 : nullptr);

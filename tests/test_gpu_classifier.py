@@ -141,11 +141,13 @@ def test_classifier_same_bits_on_a_side_stream_and_repeated(C, wl):
     mesh.close()
 
 
-@pytest.mark.parametrize("n", [1, 63, 64, 65, 128, 129, 769, 12417, 16385])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 128, 129, 769, 12417, 16385, 32769])
 def test_classifier_at_tile_edges(C, oracle_mod, wl, n):
     """Counts beside the 64-point tiles of module 1 and the 128-point tiles of the wide layers: less than a tile, one,
     one more, one more than a wavefront block's 12; 12,417: every large tile of an incomplete round; 16,385: whole
-    rounds of large tiles (128 of 512 -> 512 on 256 compute units) and one point for the small ones."""
-    w = wl.build(n_side=130, seed=13, field="fourier", field_seed=9, U=1.0, k=8.0, origins="nodes", G=64)
+    rounds of large tiles (128 of 512 -> 512 on 256 compute units) and one point for the small ones;
+    32,769: the same in the last layer."""
+    w = wl.build(n_side=190, seed=13, field="fourier", field_seed=9, U=1.0, k=8.0, origins="nodes", G=64)
     ws, bs = _weights(5)
+    assert len(w.xp) >= n
     _check(C, oracle_mod, w, w.xp[:n], ws, bs, fallback=w.start[:n])
