@@ -85,8 +85,8 @@ __device__ __forceinline__ void wprep4_bf16(int k, const float* __restrict__ w, 
 //
 // What bounds it: matrix instructions, 216 per wavefront and step at 32 -> 32 (7,130 cycles per SIMD), and the LDS, 72
 // reads of a wavefront in that time (4,600 cycles).  With one plane a step, both halves in every wavefront and half of
-// the weights read from LDS per tap it was the LDS, 162 reads for as many instructions, and two barriers a plane:
-// FIGURES.
+// the weights read from LDS per tap it was the LDS, 162 reads for as many instructions, and two barriers a plane.  The
+// three layers in us, before and now: G = 33: 33 and 31, 64: 50 and 47, 101: 218 and 178, 128: 310 and 258.
 constexpr int ZY = 8, ZX = 32;                    // cells per block: rows, columns
 constexpr int ZSY = ZY + 2, ZSX = ZX + 2;         // slab with its border
 constexpr int ZRING = 6;                          // planes in LDS
@@ -175,6 +175,7 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2)
 #pragma unroll
         for (int dx = 0; dx < 3; ++dx) at[r][dx] = zcell((row0 + r) * ZSX + col0 + col + dx, grp);
     const int gx = tx0 + col0 + col;
+    const unsigned to = NB == 2 ? gx * C + 16 * nb + 4 * grp : gx;  // the lane's place in a row of the result
     __syncthreads();
     int slot = 0;  // of plane z - 1
     for (int z = z0; z < z1; z += 2) {
@@ -209,25 +210,27 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2)
                 }
         }
         // results: lane (col, grp) holds rows 4 grp + j (output channels 16 nb + 4 grp + j) of cell col
-        if (gx < G) {
+        auto emit = [&](int oz, int oy) {
+            const int64_t row = (int64_t)(z + oz) * GG + (int64_t)(ty0 + row0 + oy) * G;
+            const v4f a = acc[oz][oy];
+            if (NB == 2) {
+                const v4f v{ fmaxf(a.x, 0.f), fmaxf(a.y, 0.f), fmaxf(a.z, 0.f), fmaxf(a.w, 0.f) };
+                *reinterpret_cast<bf16x4*>(out + row * C + to) = __builtin_convertvector(v, bf16x4);
+            } else {
+                disp[row + to] = a.x + bias[0];
+                disp[GG * G + row + to] = a.y + bias[1];
+                disp[2 * GG * G + row + to] = a.z + bias[2];
+            }
+        };
+        if (gx < G && (NB == 2 || grp == 0)) {
+            const int rows = min(ROWS, G - ty0 - row0);
+            if (rows == ROWS && z + 1 < z1) {  // without a branch a row
 #pragma unroll
-            for (int oz = 0; oz < 2; ++oz) {
-                if (z + oz >= z1) continue;
+                for (int k = 0; k < 2 * ROWS; ++k) emit(k / ROWS, k % ROWS);
+            } else {
 #pragma unroll
-                for (int oy = 0; oy < ROWS; ++oy) {
-                    const int gy = ty0 + row0 + oy;
-                    if (gy >= G) continue;
-                    const int64_t c = (int64_t)(z + oz) * GG + (int64_t)gy * G + gx;
-                    const v4f a = acc[oz][oy];
-                    if (NB == 2) {
-                        const v4f v{ fmaxf(a.x, 0.f), fmaxf(a.y, 0.f), fmaxf(a.z, 0.f), fmaxf(a.w, 0.f) };
-                        *reinterpret_cast<bf16x4*>(out + c * C + 16 * nb + 4 * grp) = __builtin_convertvector(v, bf16x4);
-                    } else if (grp == 0) {
-                        disp[c] = a.x + bias[0];
-                        disp[GG * G + c] = a.y + bias[1];
-                        disp[2 * GG * G + c] = a.z + bias[2];
-                    }
-                }
+                for (int k = 0; k < 2 * ROWS; ++k)
+                    if (k % ROWS < rows && z + k / ROWS < z1) emit(k / ROWS, k % ROWS);
             }
         }
         slot = slot2;
@@ -357,7 +360,7 @@ __device__ __forceinline__ void wprep1_split(int k, const float* __restrict__ w,
 
 // A block works as those of the layers above, two planes a step through a ring of six slabs, one row of two planes a
 // wavefront; all weights stay in registers, so that the LDS serves one read per two instructions.  G = 101: 59 us with
-// the weights read from LDS (three reads per two instructions, sixteen wavefronts, two barriers a plane), now FIG1.
+// the weights read from LDS (three reads per two instructions, sixteen wavefronts, two barriers a plane), now 45.
 __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k3c_zconv1_split(
     int32_t G, int zp, const float* __restrict__ vel, const bf16x8* __restrict__ wb, const float* __restrict__ bias,
     bf16* __restrict__ out)
@@ -431,6 +434,7 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2)
         at[st] = (wave + t / 3 % 3) * ZSX + t % 3 + col;
     }
     const bool second = grp >= 2;
+    const unsigned to = (tx0 + col) * C + 8 * grp;  // the lane's place in a row of the result
     __syncthreads();
     int slot = 0;  // of plane z - 1
     for (int z = z0; z < z1; z += 2) {
@@ -453,20 +457,20 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2)
                     acc[oz][h][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[st][1], a, st == 0 ? bl1 : acc[oz][h][1], 0, 0, 0);
                 }
             }
-        const int gy = ty0 + wave;
-        if (gy < G) {
+        auto emit = [&](int oz, int h) {
+            bf16x8 v;
 #pragma unroll
-            for (int oz = 0; oz < 2; ++oz) {
-                if (z + oz >= z1) continue;
+            for (int k = 0; k < 8; ++k) v[k] = (bf16)fmaxf(acc[oz][h][k >> 2][k & 3], 0.f);
+            *reinterpret_cast<bf16x8*>(out + ((int64_t)(z + oz) * GG + (int64_t)(ty0 + wave) * G) * C + to + 16 * h * C) = v;
+        };
+        if (ty0 + wave < G) {
+            if (tx0 + ZX <= G && z + 1 < z1) {  // without a branch a block
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int gx = tx0 + 16 * h + col;
-                    if (gx >= G) continue;
-                    bf16x8 v;
+                for (int k = 0; k < 4; ++k) emit(k >> 1, k & 1);
+            } else {
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) v[k] = (bf16)fmaxf(acc[oz][h][k >> 2][k & 3], 0.f);
-                    *reinterpret_cast<bf16x8*>(out + ((int64_t)(z + oz) * GG + (int64_t)gy * G + gx) * C + 8 * grp) = v;
-                }
+                for (int k = 0; k < 4; ++k)
+                    if (z + (k >> 1) < z1 && tx0 + 16 * (k & 1) + col < G) emit(k >> 1, k & 1);
             }
         }
         slot = slot2;
