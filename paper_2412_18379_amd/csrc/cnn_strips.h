@@ -208,7 +208,7 @@ __device__ __forceinline__ void pass(int32_t G, const Plan& plan, const float* _
                 pv[1] = *reinterpret_cast<const float*>(v + gb);
             };
             auto fetch = [&](int y) { load(vel + (int64_t)min(max(y + (wc >> 1), 0), G - 1) * G); };
-            auto stash = [&](bool row_in, int slot) {
+            auto stash = [&](const float (&pu)[2], const float (&pv)[2], bool row_in, int slot) {
                 uint32_t* to = s_vel + 2 * slot * VPITCH;
                 uint32_t* also = slot ? to : to + 6 * VPITCH;
                 const uint32_t a = f.vel(in_a && row_in ? pu[0] : 0.f, in_a && row_in ? pv[0] : 0.f);
@@ -221,11 +221,19 @@ __device__ __forceinline__ void pass(int32_t G, const Plan& plan, const float* _
             auto row_in = [&](int y) { return (unsigned)y < (unsigned)G; };
 
             if (first) {
-                fetch(yb - 1);
-                stash(row_in(yb - 1 + (wc >> 1)), 0);
-                fetch(yb + 1);
-                stash(row_in(yb + 1 + (wc >> 1)), 1);
+                float u[2][2], v[2][2];  // the first two pairs: one wait for memory
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    fetch(yb - 1 + 2 * k);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        u[k][j] = pu[j];
+                        v[k][j] = pv[j];
+                    }
+                }
                 fetch(yb + 3);
+#pragma unroll
+                for (int k = 0; k < 2; ++k) stash(u[k], v[k], row_in(yb - 1 + 2 * k + (wc >> 1)), k);
             }
             const bool out_col = oc >= 3 && oc < 3 + OW && x0 - 3 + oc < G;
             float p1 = f.sum0, p2 = f.sum0;
@@ -336,7 +344,7 @@ __device__ __forceinline__ void pass(int32_t G, const Plan& plan, const float* _
                     emit(1);
                 }
                 if (first) {
-                    stash(steady || row_in(yb + 3 + 2 * t + (wc >> 1)), sl2);
+                    stash(pu, pv, steady || row_in(yb + 3 + 2 * t + (wc >> 1)), sl2);
                     if (steady) {
                         load(ahead);
                         ahead += 2 * G;
