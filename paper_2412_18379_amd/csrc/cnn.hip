@@ -724,11 +724,11 @@ unsigned cnn_persistent_grid()
 // Which form of the FP32 pass runs.  A row block pays for its weights and halo rows, three to five rows'
 // worth, so the row form loses where its segments are a few rows long; below that, at one row a segment,
 // the tile form's single tile for a part of the compute units takes longer.  Kernels of a pass in us, tile and
-// row form: G = 33: 40.8 and 35.9, 128: 41.8 and 38.8, 160: 42.2 and 49.1, 512: 93 and 98, 700: 152 and 147,
-// 800: 181 and 187, 900: 239 and 210, 1024: 283 and 232, 1531: 583 and 479.
+// row form: G = 33: 40.8 and 33.1, 128: 41.8 and 36.2, 140: 42 and 46, 256: 44 and 53, 384: 74 and 80, 520: 106 and
+// 105, 576: 121 and 112, 700: 152 and 136, 832: 196 and 178, 1024: 283 and 219, 1531: 583 and 470.
 static bool rows_form(int32_t G)
 {
-    return G <= 128 || G >= 832;
+    return G <= 128 || G > 512;
 }
 
 size_t cnn_workspace_bytes(int32_t G, int32_t precision)

@@ -22,7 +22,7 @@ def C():
     gc.collect()  # meshes kept by reference cycles (their release synchronises the device) go now, not in a later capture
 
 
-@pytest.mark.parametrize("G", [32, 127, 128, 832, 896, 1025])
+@pytest.mark.parametrize("G", [32, 127, 128, 513, 640, 832, 896, 1025])
 def test_rows_form_full_grid(C, oracle_mod, wl, G):
     """The FP32 bar of test_gpu_cnn.py: 1e-5 relative plus 1e-5 of the channel's maximum."""
     rng = np.random.default_rng(G)
