@@ -28,6 +28,8 @@
 #include <cmath>
 
 #include "common.h"
+#include "lds_copy.h"
+#include "xcd_order.h"
 
 namespace cnnsns {
 namespace {
@@ -311,16 +313,23 @@ enum { S3_GIVEN = 0, S3_LOOKUP = 1, S3_CNN = 2 };
 // Starts: given (K_m); the overlay lookup of x_p's cell; or CNN-SNS (Alg. 2): the lookup of
 // the cell holding x_hat = clamp(x_i + D[cell(x_i)], 0, 1), falling back to the given start
 // (else element 0) where that cell holds no element.
-template <int MODE>
+template <int MODE, bool SHARED>
 __global__ __launch_bounds__(kBlock) void k3_locate(const TetRec* __restrict__ rec, int64_t n_tet, int64_t n,
                                                     const double* __restrict__ xp, const int32_t* __restrict__ start,
                                                     const double* __restrict__ origin, const float* __restrict__ disp,
                                                     const int32_t* __restrict__ lookup, int32_t G, int32_t max_iter,
                                                     int32_t* __restrict__ host, int32_t* __restrict__ iters,
-                                                    uint8_t* __restrict__ status)
+                                                    uint8_t* __restrict__ status, XcdOrder order)
 {
-    const int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= n) return;
+    // SHARED: records by way of LDS.  In copy k of eight, each eight lanes fetch the record of their lane k, 16 bytes each;
+    // a copy lies 65 16-byte places after the one before, so that lanes reading the same part use distinct banks.
+    constexpr int kCopy = 65 * 16;
+    __shared__ __attribute__((aligned(16))) char s_rec[SHARED ? kBlock / 64 : 1][SHARED ? 8 * kCopy : 16];
+    const int lane = threadIdx.x & 63;
+    char* const my_rec = s_rec[SHARED ? threadIdx.x / 64 : 0];
+    const int64_t point = (int64_t)(SHARED ? order.block() : blockIdx.x) * kBlock + threadIdx.x;
+    if (!SHARED && point >= n) return;
+    const int64_t idx = point < n ? point : n - 1;  // lanes past the last point: not walked, not written
     const double3 p{ xp[3 * idx], xp[3 * idx + 1], xp[3 * idx + 2] };
     int32_t K;
     if (MODE == S3_GIVEN) {
@@ -337,25 +346,46 @@ __global__ __launch_bounds__(kBlock) void k3_locate(const TetRec* __restrict__ r
         K = lookup[((int64_t)cell3(q.z, G) * G + cell3(q.y, G)) * G + cell3(q.x, G)];
         if (K < 0) K = (MODE == S3_CNN && start) ? start[idx] : 0;  // a cell with no element
     }
-    if (K < 0 || K >= n_tet) {
-        host[idx] = -1;
-        if (iters) iters[idx] = 0;
-        if (status) status[idx] = CNNSNS_BADSTART;
-        return;
-    }
+    bool active = point < n;
     int32_t I = 0;
-    int fin;
+    int fin = CNNSNS_BADSTART;
+    if (K < 0 || K >= n_tet) {
+        K = -1;
+        active = false;
+    }
     for (;;) {
+        if (SHARED) {
+            if (__ballot(active) == 0) break;
+            const int at = active ? K : 0;
+            const char* part = reinterpret_cast<const char*>(rec) + 16 * (lane & 7);
+            const bool high = lane & 4;
+            auto copy = [&](int e, int k) { lds_copy16(part + (int64_t)e * (int64_t)sizeof(TetRec), my_rec + k * kCopy); };
+            auto both = [&](int b, int k) {  // b: lane k of each quad, in the whole quad
+                const int m = __builtin_amdgcn_mov_dpp(b, 0x141, 0xf, 0xf, true);  // the other quad of the eight
+                copy(high ? m : b, k);
+                copy(high ? b : m, k + 4);
+            };
+            both(__builtin_amdgcn_mov_dpp(at, 0x00, 0xf, 0xf, true), 0);
+            both(__builtin_amdgcn_mov_dpp(at, 0x55, 0xf, 0xf, true), 1);
+            both(__builtin_amdgcn_mov_dpp(at, 0xaa, 0xf, 0xf, true), 2);
+            both(__builtin_amdgcn_mov_dpp(at, 0xff, 0xf, 0xf, true), 3);
+            lds_copies_arrived();
+            if (!active) continue;
+        } else if (!active) {
+            break;
+        }
         I = I + 1;
         double3 v[4];
         int32_t nb[4], o;
         uint32_t pos;
-        load_tet(rec, K, v, nb, o, pos);
+        load_tet(SHARED ? reinterpret_cast<const TetRec*>(my_rec + (lane & 7) * kCopy + (lane >> 3) * (int)sizeof(TetRec)) : rec + K,
+                 0, v, nb, o, pos);
         double s[4];
         numerators(p, v, o, s);
         if (s[0] >= 0.0 && s[1] >= 0.0 && s[2] >= 0.0 && s[3] >= 0.0) {
             fin = CNNSNS_FOUND;
-            break;
+            active = false;
+            continue;
         }
         // eq. (5): the smallest coordinate, ties to the lowest position in the element order
         double sm = s[0];
@@ -372,14 +402,16 @@ __global__ __launch_bounds__(kBlock) void k3_locate(const TetRec* __restrict__ r
         }
         if (m == -1) {
             fin = CNNSNS_OUTSIDE;
-            break;
+            active = false;
+            continue;
         }
         K = m;
         if (I >= max_iter) {
             fin = CNNSNS_MAXITER;
-            break;
+            active = false;
         }
     }
+    if (point >= n) return;
     host[idx] = K;
     if (iters) iters[idx] = I;
     if (status) status[idx] = (uint8_t)fin;
@@ -535,6 +567,14 @@ void destroy_mesh3(cnnsns_mesh3 m)
     delete m;
 }
 
+// From given starts with six wavefronts a compute unit or more, records come through LDS and blocks in chunks per XCD: the
+// L1 is what bounds the walk, 512 lookups a hop for 64 records of eight 16-byte loads, one a cycle, where eight lanes
+// that fetch a record together need 128.  With fewer wavefronts a hop's latency counts, which the LDS adds to.  Every
+// vertex, 10 diameters, in us, directly and so: 64k points 92 and 110, 104k 144 and 125, 166k 212 and 162, 373k 395 and
+// 350, 970k 1,005 and 900.  The walks from looked-up starts are short and stay as they are (373k points: 29.5 us in
+// order, 28.4 by XCD).
+constexpr int64_t kSharedBlocks = 384;
+
 void launch_locate3(const cnnsns_mesh3_s& m, int64_t n, const double* xp, const int32_t* start, const double* origin,
                     const float* disp, int32_t max_iter, int32_t* host, int32_t* iters, uint8_t* status,
                     hipStream_t stream)
@@ -543,16 +583,19 @@ void launch_locate3(const cnnsns_mesh3_s& m, int64_t n, const double* xp, const 
     if (max_iter <= 0) max_iter = 1 << 20;
     const int64_t blocks = (n + kBlock - 1) / kBlock;
     if (blocks > (int64_t)INT32_MAX) fail(CNNSNS_EINVAL, "locate3d: too many points");
-    const unsigned g = (unsigned)blocks;
+    const XcdOrder order((unsigned)blocks, 192);
+    auto run = [&](auto kernel, unsigned grid) {
+        kernel<<<grid, kBlock, 0, stream>>>(m.rec, m.n_tet, n, xp, start, origin, disp, m.lookup, m.G, max_iter, host, iters,
+                                            status, order);
+    };
     if (disp)
-        k3_locate<S3_CNN><<<g, kBlock, 0, stream>>>(m.rec, m.n_tet, n, xp, start, origin, disp, m.lookup, m.G,
-                                                    max_iter, host, iters, status);
-    else if (start)
-        k3_locate<S3_GIVEN><<<g, kBlock, 0, stream>>>(m.rec, m.n_tet, n, xp, start, origin, disp, m.lookup, m.G,
-                                                      max_iter, host, iters, status);
+        run(k3_locate<S3_CNN, false>, order.blocks);
+    else if (!start)
+        run(k3_locate<S3_LOOKUP, false>, order.blocks);
+    else if (blocks < kSharedBlocks)
+        run(k3_locate<S3_GIVEN, false>, order.blocks);
     else
-        k3_locate<S3_LOOKUP><<<g, kBlock, 0, stream>>>(m.rec, m.n_tet, n, xp, start, origin, disp, m.lookup, m.G,
-                                                       max_iter, host, iters, status);
+        run(k3_locate<S3_GIVEN, true>, order.grid());
     hip_check(hipGetLastError(), "locate3d launch");
 }
 

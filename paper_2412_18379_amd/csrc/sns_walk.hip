@@ -15,6 +15,8 @@
 #pragma clang fp contract(off)
 
 #include "common.h"
+#include "lds_copy.h"
+#include "xcd_order.h"
 
 namespace cnnsns {
 namespace {
@@ -39,19 +41,24 @@ __device__ __forceinline__ double clamp01(double v)
 // element (the step after eq. 4 of Sec. 2.1), from the barycentric numerators of the last iteration:
 // out = sum_j (s_j / |S_0|) nodal[node j], summed in the element's counter-clockwise node order,
 // exactly as cnnsns_interpolate computes it.
-template <int MODE, bool INTERP>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_locate(const ElemRec* __restrict__ rec, int64_t n_tri, int64_t n,
+enum { kInOrder = 0, kByXcd = 1, kShared = 2 };  // how the points' blocks are taken (launch_mode)
+
+template <int MODE, bool INTERP, int WALK>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WALK == kShared && INTERP ? 7 : 8))) void k_locate(const ElemRec* __restrict__ rec, int64_t n_tri, int64_t n,
                                                    const double2* __restrict__ xp, const int32_t* __restrict__ start,
                                                    const double2* __restrict__ origin,
                                                    const float* __restrict__ disp,
                                                    const int32_t* __restrict__ lookup, int32_t G, int32_t max_iter,
                                                    int32_t* __restrict__ host, int32_t* __restrict__ iters,
                                                    uint8_t* __restrict__ status, const int3* __restrict__ tri,
-                                                   const double2* __restrict__ nodal, double2* __restrict__ out)
+                                                   const double2* __restrict__ nodal, double2* __restrict__ out,
+                                                   XcdOrder order)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t wave = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
-    const int64_t n_waves = (int64_t)gridDim.x * (kBlock / kWave);
+    const unsigned block = WALK == kInOrder ? blockIdx.x : order.block(), blocks = WALK == kInOrder ? gridDim.x : order.blocks;
+    if (WALK != kInOrder && block >= blocks) return;
+    const int64_t wave = ((int64_t)block * kBlock + threadIdx.x) / kWave;
+    const int64_t n_waves = (int64_t)blocks * (kBlock / kWave);
     // From the element before movement (long paths, where neighbouring points share elements)
     // a wave owns kChunkGiven slots: slot v is point wave kChunkGiven + v, a contiguous chunk.
     // From a looked-up start (short paths, whose rare long ones cluster at the two ends of the
@@ -131,6 +138,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
         __builtin_amdgcn_wave_barrier();  // LDS operations of one wavefront complete in order
     }
 
+    // kShared: records by way of LDS.  In copy k of four, the four lanes of each quad fetch the record of their lane k,
+    // 16 bytes each: the wavefront's records, quad by quad, a copy's 65 16-byte places after the one before (so that lanes
+    // reading the same quarter of their records use distinct banks).
+    constexpr bool SHARED = WALK == kShared;
+    constexpr int kCopy = 65 * 16;
+    __shared__ __attribute__((aligned(16))) char s_rec[SHARED ? kBlock / kWave : 1][SHARED ? 4 * kCopy : 16];
+    char* const my_rec = s_rec[SHARED ? threadIdx.x / kWave : 0];
+
     bool active = false;
     int64_t idx = 0;
     int64_t slot = 0;  // the lane's current slot (lookup-started modes)
@@ -175,11 +190,23 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
             if (next >= n_slots) break;
             continue;
         }
+        if (SHARED) {
+            const int at = active ? K : 0;
+            const char* quarter = reinterpret_cast<const char*>(rec) + 16 * (lane & 3);
+            auto copy = [&](int e, int k) { lds_copy16(quarter + (int64_t)e * (int64_t)sizeof(ElemRec), my_rec + k * kCopy); };
+            copy(__builtin_amdgcn_mov_dpp(at, 0x00, 0xf, 0xf, true), 0);  // lane 0 of each quad to all four
+            copy(__builtin_amdgcn_mov_dpp(at, 0x55, 0xf, 0xf, true), 1);
+            copy(__builtin_amdgcn_mov_dpp(at, 0xaa, 0xf, 0xf, true), 2);
+            copy(__builtin_amdgcn_mov_dpp(at, 0xff, 0xf, 0xf, true), 3);
+            lds_copies_arrived();
+        }
         if (active) {
             I = I + 1;
-            const double2* r2 = reinterpret_cast<const double2*>(rec + K);
+            const char* const r = SHARED ? my_rec + (lane & 3) * kCopy + (lane >> 2) * (int)sizeof(ElemRec)
+                                         : reinterpret_cast<const char*>(rec + K);
+            const double2* r2 = reinterpret_cast<const double2*>(r);
             const double2 A = r2[0], B = r2[1], C = r2[2];
-            const int4 nb = reinterpret_cast<const int4*>(rec + K)[3];
+            const int4 nb = reinterpret_cast<const int4*>(r)[3];
             // barycentric numerators s_j = |S_j| (Sec. 2.2), vertex j's column replaced by x_p
             const double adx = A.x - px, ady = A.y - py;
             const double bdx = B.x - px, bdy = B.y - py;
@@ -326,16 +353,32 @@ void launch_interp(const cnnsns_mesh_s& m, int64_t n, const double* xp, const in
     hip_check(hipGetLastError(), "interpolate launch");
 }
 
+// In order of id below 64 blocks (a walk of 1,922 points: 9.4 us, 9.7 with the reordering's few instructions); by XCD from
+// there; and from given starts with 24 wavefronts a compute unit or more also through LDS.  There the L1 is what bounds
+// the walk: it looks up one line a cycle, 256 a hop for 64 records of four 16-byte loads, where four lanes that
+// fetch a record together need 64.  With fewer wavefronts a hop's latency counts, which the LDS adds to.  Every centroid,
+// 20 diameters, in us, in order, by XCD and through LDS: 250k points 76, 65 and 71, 500k 134, 119 and 98, 1M 294, 283
+// and 235; CNN starts, in order and by XCD: 1M 20.1 and 18.0, 2M 36.7 and 32.9, 4M 78.8 and 77.5.
+constexpr int64_t kSharedWaves = 6144;
+
 template <int MODE, bool INTERP>
 static void launch_mode(const cnnsns_mesh_s& m, int64_t n, const double2* xp2, const int32_t* start,
                         const double2* or2, const float* disp, int32_t max_iter, int32_t* host, int32_t* iters,
                         uint8_t* status, const double* nodal, double* out, unsigned blocks, hipStream_t stream)
 {
-    k_locate<MODE, INTERP><<<blocks, kBlock, 0, stream>>>(m.rec, m.n_tri, n, xp2, start, or2, disp, m.lookup, m.G,
-                                                           max_iter, host, iters, status,
-                                                           reinterpret_cast<const int3*>(m.tri),
-                                                           reinterpret_cast<const double2*>(nodal),
-                                                           reinterpret_cast<double2*>(out));
+    const XcdOrder order(blocks, MODE == START_GIVEN ? 128 : 64);
+    auto run = [&](auto kernel) {
+        kernel<<<order.grid(), kBlock, 0, stream>>>(m.rec, m.n_tri, n, xp2, start, or2, disp, m.lookup, m.G, max_iter, host,
+                                                    iters, status, reinterpret_cast<const int3*>(m.tri),
+                                                    reinterpret_cast<const double2*>(nodal), reinterpret_cast<double2*>(out),
+                                                    order);
+    };
+    if (order.chunk == 0)
+        run(k_locate<MODE, INTERP, kInOrder>);
+    else if (MODE != START_GIVEN || (int64_t)blocks * (kBlock / kWave) < kSharedWaves)
+        run(k_locate<MODE, INTERP, kByXcd>);
+    else
+        run(k_locate<START_GIVEN, INTERP, kShared>);
 }
 
 void launch_locate(const cnnsns_mesh_s& m, int64_t n, const double* xp, const int32_t* start, const double* origin,

@@ -1,0 +1,32 @@
+// The order in which a walk's blocks take the points.
+//
+// Workgroups go to the 8 XCDs round-robin by id, each with an L2 of its own; consecutive blocks of points, whose paths
+// share elements, would so meet in no cache.  Here each XCD takes chunks of consecutive blocks instead, chunk by chunk
+// in turn: chunks as long as `longest` allows, all of nearly the same length (one chunk per XCD would leave an XCD
+// with the longest walks of the point order to run alone at the end).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace cnnsns {
+
+struct XcdOrder {
+    unsigned blocks, chunk;  // chunk 0: in order of id, for walks of a few blocks an XCD
+    XcdOrder(unsigned n, unsigned longest) : blocks(n), chunk(0)
+    {
+        if (n <= 64) return;
+        const unsigned per = n / 8 + (n % 8 != 0);  // blocks of an XCD
+        const unsigned chunks = per / longest + (per % longest != 0);
+        chunk = per / chunks + (per % chunks != 0);
+    }
+    // workgroups to launch: whole rounds of a chunk on every XCD
+    unsigned grid() const { return chunk ? (blocks + 8 * chunk - 1) / (8 * chunk) * (8 * chunk) : blocks; }
+    // this workgroup's block of points (chunk > 0); those past the last one have none
+    __device__ __forceinline__ unsigned block() const
+    {
+        const unsigned r = blockIdx.x / 8;
+        return (r / chunk * 7 + blockIdx.x % 8) * chunk + r;
+    }
+};
+
+}  // namespace cnnsns
