@@ -35,6 +35,7 @@ CNN_MACS_PER_PIXEL = 2 * 32 * 9 + 32 * 32 * 9 * 2 + 32 * 2 * 9  # 19,584
 # Winograd F(2x2,3x3) multiplies per output pixel and channel pair: 16 per 2 x 2 block; the MACs it
 # saves are not counted as useful work
 WINO_USEFUL_MACS_PER_PIXEL = 2 * 32 * 9 + 2 * 32 * 32 * 4 + 32 * 2 * 9  # 9,344
+ROWS_USEFUL_MACS_PER_PIXEL = 2 * 32 * 9 + 2 * 32 * 32 * 6 + 32 * 2 * 9  # 13,440: F(2,3) along a row
 
 
 def _cdiv(a, b):
@@ -74,10 +75,63 @@ def _cus() -> int:
     return torch.cuda.get_device_properties(0).multi_processor_count
 
 
+def f32_rows(G: int) -> bool:
+    """Whether the FP32 pass on G x G cells takes its row form (BF16 matrix instructions on operands split into
+    three BF16 values), not its tile form (FP32 matrix instructions)."""
+    return G <= 128 or G > 512
+
+
+def _row_blocks(G: int, cus: int):
+    """(wavefronts with columns inside the grid, rows) of each block of the FP32 pass's row form: strips of
+    256 columns in segments of rows, as the kernels' host code plans them."""
+    strips = _cdiv(G, 256)
+    full, lastw = strips - 1, G - (strips - 1) * 256
+    t = 0.62 if lastw <= 128 else 1.0
+    best = None
+    for nl in range(1, (cus - full if cus > strips else 1) + 1):
+        nf = max((cus - nl) // full, 1) if full else 1
+        rf, rl = _cdiv(G, nf), _cdiv(G, nl)
+        cost = max(t * (rl + 3), rf + 3.0 if full else 0.0)
+        if best is None or cost < best[0]:
+            best = (cost, rf, rl)
+    _, rf, rl = best
+    for strip in range(strips):
+        rows, waves = (rl if strip == strips - 1 else rf), _cdiv(min(256, G - 256 * strip), 32)
+        for r0 in range(0, G, rows):
+            yield waves, min(rows, G - r0)
+
+
+def _strip_steps(G: int, cus: int):
+    """Row pairs of conv3 of each run of rows of the BF16 and FP8 passes: strips of 122 output columns, in segments
+    or end to end, as the kernels' host code plans them."""
+    strips = _cdiv(G, 122)
+    segs, per = cus // strips, 2 * _cdiv(_cdiv(strips * G, cus), 2)
+    if segs:
+        rows = 2 * _cdiv(_cdiv(G, segs), 2)
+        if rows // 2 + 4 <= per // 2 + 8:
+            for r0 in range(0, G, rows):
+                for _ in range(strips):
+                    yield (min(rows, G - r0) + 3) // 2
+            return
+    u = 0
+    while u < strips * G:
+        end = min(u // per * per + per, (u // G + 1) * G)
+        yield (end - u + 3) // 2
+        u = end
+
+
 def cnn_issued_macs(G: int, precision: str) -> float:
-    """Matrix-core MACs one forward pass issues over a G x G overlay, padding and recomputed halos
-    included (per tile, as the kernels are written)."""
+    """Matrix-core MACs one forward pass issues over a G x G overlay, padding, recomputed halos and the
+    six products per FP32 product of the split form included (as the kernels are written)."""
     cdiv = _cdiv
+    if precision == "f32" and f32_rows(G):
+        # 16 x 16 x 32 instructions: a wavefront's 32 columns of a row take 144 of a 32 -> 32 layer (F(2,3) along the
+        # row: 12 stages of 12), 20 of conv1 (one block more in turn among the wavefronts), 24 of conv4
+        n = 0
+        for waves, rows in _row_blocks(G, _cus()):
+            n += waves * 144 * (rows + 2) + (8 * 20 + 10) * (rows + 2)
+            n += waves * (144 * (rows + 4) + 24 * (rows + 2))
+        return n * 16 * 16 * 32
     if precision == "f32":
         regions12 = cdiv(G, 32) * cdiv(G, 16)  # 16 x 32 regions: conv1 (K 18 -> 20) on the 39 M-blocks of
         tiles34 = conv34_tiles(G, _cus())      # the 18 x 34 input tile, then conv2 as Winograd F(2x2,3x3);
@@ -85,22 +139,25 @@ def cnn_issued_macs(G: int, precision: str) -> float:
         return (regions12 * (624 * 20 * 32 + 128 * 16 * 32 * 32) +
                 tiles34 * (128 * 16 * 32 * 32 + 512 * 32 * 16))
     if precision == "bf16":
-        tiles = cdiv(G, 30) * cdiv(G, 14)  # fused 14 x 30 output tiles: conv1 (K 32) on 20 x 36 pixels,
-        # conv2 on 40 M-blocks (18 x 34 pixels), conv3 on 32 (16 x 32), conv4 as 32 columns of K 32
-        return tiles * (720 * 32 * 32 + 640 * 288 * 32 + 512 * 288 * 32 + 512 * 32 * 32)
+        # four pairs of wavefronts, 32 columns and two rows a step: 8 instructions of conv1 and of conv4, 72 of
+        # conv2 and of conv3; conv1 runs two row pairs more than conv3, conv2 one
+        n = sum(4 * (8 * (j + 2) + 72 * (j + 1) + 72 * j + 8 * j) for j in _strip_steps(G, _cus()))
+        return n * 16 * 16 * 32
     raise ValueError(precision)
 
 
-# the classifier CNN (Sec. 2.3) per point: matrix-core MACs issued (conv1 on 96 rows of 16 x 20, conv2 on
-# 96 rows of 16 x 144, the FC layers 256 x 256, 512 x 512 and 512 x 128 with the 81 logits padded to two
-# 64-column tiles) and the products the network needs (module 2's first layer runs on the vector ALUs)
-CLS_ISSUED_MACS = 96 * 20 * 16 + 96 * 144 * 16 + 256 * 256 + 512 * 512 + 512 * 128  # 645,120
+# the classifier CNN (Sec. 2.3) per point: matrix-core MACs issued on the BF16 instruction, six per FP32
+# product (conv2 on the 64 pooled cells, K 144 -> 160, the FC layers 256 x 256, 512 x 512 and 512 x 96 with the 81
+# logits padded; conv1, 30 FP32 instructions, and module 2's first layer, on the vector ALUs, besides) and the
+# products the network needs
+CLS_ISSUED_MACS = 6 * (64 * 160 * 16 + 256 * 256 + 512 * 512 + 512 * 96)  # 3,244,032
 CLS_USEFUL_MACS = 81 * 18 * 16 + 81 * 144 * 16 + 2 * 256 + 256 * 256 + 512 * 512 + 512 * 81  # 579,616
 REC_BYTES = 60  # algorithmic bytes of one element record: 6 FP64 coordinates + 3 int32 neighbours
 # one tetrahedron record: 12 FP64 coordinates, 4 int32 neighbours and the 4 int32 node ids that put
 # each face's nodes in a fixed order
 TET_REC_BYTES = 128
 CNN3_MACS_PER_CELL = 3 * 32 * 27 + 2 * 32 * 32 * 27 + 32 * 3 * 27  # 60,480
+CNN3_SPLIT_MACS_PER_CELL = 6 * 2 * 32 * 32 * 27  # the FP32 pass's 32 -> 32 layers, six BF16 products per FP32 product
 
 
 def log(msg):
@@ -316,6 +373,7 @@ def walk3d_leg(name: str, K: int, warmup: int, copy_gbps: float, with_cpu: bool 
     log(f"3D CNN-SNS: predict {p3_ms.mean():.3f} ms, locate {l3_ms.mean():.3f} ms, mean I_t {it_c.mean():.2f}")
     cnn3_flops = 2.0 * CNN3_MACS_PER_CELL * w.G ** 3
     cnn3_tf = cnn3_flops / (p3_ms.mean() / 1e3) / 1e12
+    cnn3_issued_tf = cnn3_tf * CNN3_SPLIT_MACS_PER_CELL / CNN3_MACS_PER_CELL
     d32 = disp.cpu().numpy()
     # the same step with the BF16 3D CNN (precision variant)
     for _ in range(warmup):
@@ -383,12 +441,15 @@ def walk3d_leg(name: str, K: int, warmup: int, copy_gbps: float, with_cpu: bool 
                     "path_length_p50_p99_max": [pct(it_c, 50), pct(it_c, 99), int(it_c.max())],
                     "found_frac": float(np.mean(st_c == C.FOUND)),
                     "host_agreement_with_plain": float(np.mean(host_c == host_p)),
-                    "cnn_roofline": {"kernel": "3D cnn forward (k3c_zconv1 + 2 x k3c_conv32 + k3c_zconv4_f32)",
-                                     "bound": "mfma", "achieved": round(cnn3_tf, 3), "peak": PEAK["f32_TFLOPs"],
-                                     "unit": "TFLOP/s", "frac": round(cnn3_tf / PEAK["f32_TFLOPs"], 4),
+                    "cnn_roofline": {"kernel": "3D cnn forward (k3c_zconv1 + 2 x k3c_zsplit_f32 + k3c_zconv4_f32)",
+                                     "bound": "mfma", "achieved": round(cnn3_issued_tf, 3), "peak": PEAK["bf16_TFLOPs"],
+                                     "unit": "TFLOP/s", "frac": round(cnn3_issued_tf / PEAK["bf16_TFLOPs"], 4),
+                                     "direct_conv_equivalent": round(cnn3_tf, 3),
                                      "traffic": traffic_for("cnn3_forward_f32", name),
                                      "algorithmic_per_launch": f"{cnn3_flops:.4e} FLOP (2 x 60480 MAC x G^3, "
-                                                               f"G={w.G})"}},
+                                                               f"G={w.G}); achieved: the 32 -> 32 layers' "
+                                                               f"{CNN3_SPLIT_MACS_PER_CELL} MAC per cell issued on "
+                                                               f"the BF16 matrix cores"}},
         "cnn_sns_bf16": {"predict_ms": round(float(pb_ms.mean()), 4), "locate_ms": round(float(lb_ms.mean()), 4),
                          "step_ms": round(float((pb_ms + lb_ms).mean()), 4),
                          "speedup_vs_plain_sns": round(float(plain_ms.mean() / (pb_ms + lb_ms).mean()), 4),
@@ -742,11 +803,12 @@ def classifier_leg(C, T, w, mesh, xp, start, K: int, warmup: int, plain_ms: floa
         "speedup_vs_plain_sns": round(float(plain_ms / (cls_ms + loc_ms).mean()), 4),
         "mean_path_length": round(float(it.mean()), 3),
         "path_length_p50_p99_max": [pct(it, 50), pct(it, 99), int(it.max())],
-        "roofline": {"kernel": "cnnsns_classify (k_cls_module1 + 3 x k_dense_f32 + k_cls_argmax)", "bound": "mfma",
-                     "achieved": round(issued, 3), "peak": PEAK["f32_TFLOPs"], "unit": "TFLOP/s",
-                     "frac": round(issued / PEAK["f32_TFLOPs"], 4),
+        "roofline": {"kernel": "cnnsns_classify (k_cls_module1 + 3 x k_dense_split + k_cls_argmax)", "bound": "mfma",
+                     "achieved": round(issued, 3), "peak": PEAK["bf16_TFLOPs"], "unit": "TFLOP/s",
+                     "frac": round(issued / PEAK["bf16_TFLOPs"], 4),
                      "algorithmic_per_launch": f"{2.0 * CLS_ISSUED_MACS * n:.4e} FLOP issued ({CLS_ISSUED_MACS} MAC "
-                                               f"per point on the matrix cores; {CLS_USEFUL_MACS} needed)"},
+                                               f"per point on the BF16 matrix cores, six per FP32 product; "
+                                               f"{CLS_USEFUL_MACS} needed)"},
     }
 
 
@@ -920,7 +982,8 @@ def main():
     value = n / (ms_step / 1e3)
     G = w.G
     cnn_flops = 2.0 * CNN_MACS_PER_PIXEL * G * G
-    cnn_peak = PEAK[{"f32": "f32_TFLOPs", "bf16": "bf16_TFLOPs", "fp8": "fp8_TFLOPs"}[precision]]
+    rows = precision == "f32" and f32_rows(G)
+    cnn_peak = PEAK["bf16_TFLOPs" if rows else {"f32": "f32_TFLOPs", "bf16": "bf16_TFLOPs", "fp8": "fp8_TFLOPs"}[precision]]
     cnn_tf = cnn_flops / (pred_ms.mean() / 1e3) / 1e12
     # walk algorithmic bytes: one element record per iteration plus per-point inputs and outputs
     out_b = 4 + 4 + 1
@@ -929,16 +992,19 @@ def main():
     gbps_cnn_walk = bytes_cnn_walk / (loc_ms.mean() / 1e3) / 1e9
     gbps_plain = bytes_plain / (plain_ms.mean() / 1e3) / 1e9
     issued_tf = 2.0 * cnn_issued_macs(G, precision) / (pred_ms.mean() / 1e3) / 1e12
-    useful_macs = (WINO_USEFUL_MACS_PER_PIXEL if precision == "f32" else CNN_MACS_PER_PIXEL) * G * G
+    useful_macs = (ROWS_USEFUL_MACS_PER_PIXEL if rows else WINO_USEFUL_MACS_PER_PIXEL if precision == "f32" else
+                   CNN_MACS_PER_PIXEL) * G * G
     roofline = {
-        "kernel": {"f32": "cnn forward (k_conv12_f32 + k_conv34_f32, one cnnsns_predict)",
+        "kernel": {"f32": ("cnn forward (k_rows12_f32 + k_rows34_f32, one cnnsns_predict)" if rows else
+                           "cnn forward (k_conv12_f32 + k_conv34_f32, one cnnsns_predict)"),
                    "bf16": "cnn forward (k_cnn_bf16, one cnnsns_predict)"}.get(precision, "cnn forward"),
         "bound": "mfma", "achieved": round(issued_tf, 3), "peak": cnn_peak, "unit": "TFLOP/s",
         "frac": round(issued_tf / cnn_peak, 4),
         "traffic": traffic_for(f"cnn_forward_{precision}", args.workload),
         "algorithmic_per_launch": (f"{2 * cnn_issued_macs(G, precision):.4e} FLOP issued on the matrix cores "
                                    f"(G={G}: {cnn_issued_macs(G, precision) / (G * G):.0f} MAC per cell with "
-                                   f"padding, recomputed halos and, in FP32, the Winograd form)"),
+                                   f"padding, recomputed halos and, in FP32, " +
+                                   ("F(2,3) with six BF16 products per FP32 product)" if rows else "the Winograd form)")),
         "useful_work": {"macs_per_cell": useful_macs // (G * G),
                         "achieved": round(2.0 * useful_macs / (pred_ms.mean() / 1e3) / 1e12, 3),
                         "frac": round(2.0 * useful_macs / (pred_ms.mean() / 1e3) / 1e12 / cnn_peak, 4),
@@ -1045,7 +1111,7 @@ def main():
         lb = np.array([eb[k][1].elapsed_time(eb[k][2]) for k in range(K)])
         it_b = iters_b.cpu().numpy()
         pk = PEAK[f"{vp}_TFLOPs"]
-        issued = 2.0 * cnn_issued_macs(G, "bf16")  # the FP8 pass has the BF16 pass's tiling
+        issued = 2.0 * cnn_issued_macs(G, "bf16")  # the FP8 pass is the BF16 pass's pipeline
         res[f"{vp}_variant"] = {
             "points_per_s": round(n / wall_b * K, 1), "ms_per_step": round(wall_b * 1e3 / K, 4),
             "predict_ms": round(float(pb.mean()), 4), "locate_ms": round(float(lb.mean()), 4),
