@@ -358,17 +358,20 @@ void launch_interp(const cnnsns_mesh_s& m, int64_t n, const double* xp, const in
 // the walk: it looks up one line a cycle, 256 a hop for 64 records of four 16-byte loads, where four lanes that
 // fetch a record together need 64.  With fewer wavefronts a hop's latency counts, which the LDS adds to.  Every centroid,
 // 20 diameters, in us, in order, by XCD and through LDS: 250k points 76, 65 and 71, 500k 134, 119 and 98, 1M 294, 283
-// and 235; CNN starts, in order and by XCD: 1M 20.1 and 18.0, 2M 36.7 and 32.9, 4M 78.8 and 77.5.
+// and 235; CNN starts, in order and by XCD: 0.5M 20.3 and 18.0, 1M 36.7 and 33.2, 2M 77.2 and 76.4.
+// Looked-up starts go in order again past 6,144 blocks, whose short walks have little left to share: 4M points 168.6
+// and 169.5, ASG starts 139 and 140.
 constexpr int64_t kSharedWaves = 6144;
+constexpr unsigned kOrderedBlocks = 6144;
 
 template <int MODE, bool INTERP>
 static void launch_mode(const cnnsns_mesh_s& m, int64_t n, const double2* xp2, const int32_t* start,
                         const double2* or2, const float* disp, int32_t max_iter, int32_t* host, int32_t* iters,
                         uint8_t* status, const double* nodal, double* out, unsigned blocks, hipStream_t stream)
 {
-    const XcdOrder order(blocks, MODE == START_GIVEN ? 128 : 64);
+    const XcdOrder order(MODE == START_GIVEN || blocks <= kOrderedBlocks ? blocks : 0, MODE == START_GIVEN ? 128 : 32);
     auto run = [&](auto kernel) {
-        kernel<<<order.grid(), kBlock, 0, stream>>>(m.rec, m.n_tri, n, xp2, start, or2, disp, m.lookup, m.G, max_iter, host,
+        kernel<<<order.chunk ? order.grid() : blocks, kBlock, 0, stream>>>(m.rec, m.n_tri, n, xp2, start, or2, disp, m.lookup, m.G, max_iter, host,
                                                     iters, status, reinterpret_cast<const int3*>(m.tri),
                                                     reinterpret_cast<const double2*>(nodal), reinterpret_cast<double2*>(out),
                                                     order);
