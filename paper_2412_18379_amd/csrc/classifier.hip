@@ -22,8 +22,8 @@
 //
 // On the GPU: one wavefront per particle for module 1 (window gather, both
 // convolutions on the matrix cores, pooling) and module 2's first layer; the three wide FC layers as
-// batched FP32 matrix products over a chunk of particles
-// (v_mfma_f32_16x16x4f32, 64 x 64 output tiles); then the argmax and start.
+// batched matrix products over a chunk of particles, FP32 values as three BF16 ones (split.h); then the argmax and
+// start.
 #pragma clang fp contract(off)
 
 #include <hipcub/hipcub.hpp>

@@ -2,26 +2,14 @@
 // overlay): 3 -> 32 -> 32 -> 32 -> 3 channels, zero padding of one cell, bias,
 // ReLU after layers 1-3, FP32.
 //
-// Layers 2 and 3 (32 -> 32, 94 % of the work) are dense contractions over
-// 27 taps x 32 input channels per output cell and run on the matrix cores
-// (v_mfma_f32_16x16x4f32, D = A B): A holds the weights (row = output
-// channel, k = input channel), B the input activations (column = one of 16
-// consecutive cells along x, k = input channel).  Lane l supplies output
-// channel 16 nb + l%16 (A) and cell l%16 (B), both for input channel
-// 8 (l/16) + 4h + j in k-step j of channel half h, and receives output
-// channels 16 nb + 4 (l/16) + r (r = 0..3) of cell l%16: four consecutive
-// channels, stored as one 16-byte write.  A wavefront computes 64 cells of one
-// x row (four 16-cell blocks) for all 32 output channels; the 27 taps' weights
-// sit in LDS in operand order (108 KiB, loaded once per block), the
-// activations come through the caches (a cell's 32 channels are one 128-byte
-// line).  Layers 1 and 4 (3 -> 32, 32 -> 3) are 9 % of the work.  Layer 1 runs
-// on the matrix cores in FP32 as a z-sweep (k3c_zconv1: three velocity planes
-// staged in LDS, K = one tap's three components and a zero); layer 4 reads its
-// input once per plane in a z-sweep and runs on the vector ALUs in FP32
-// (k3c_zconv4_f32).  The BF16 pass (BF16
-// operands after layer 1, FP32 accumulation) runs layers 2-4 as z-sweeps that
-// stage three input planes at a time in LDS (described before
-// k3c_zsweep_bf16), layer 4 with its 3 outputs padded to 16.
+// All layers run as z-sweeps: a block owns a column of 8 x 32 cells and consecutive planes and keeps the input planes
+// that its current outputs read, with their one-cell border, in LDS.  Layers 2 and 3 (32 -> 32, 94 % of the work) are
+// dense contractions over 27 taps x 32 input channels per output cell on the matrix cores, with the weights as row
+// operand and 16 consecutive cells along x as column operand, so that a lane ends with consecutive channels of
+// one cell.  FP32 pass: layers 2 and 3 on BF16 instructions with three BF16 values per FP32 value (k3c_zsplit_f32,
+// split.h), layer 1 (k3c_zconv1) and layer 4 (k3c_zconv4_f32) on the FP32 instruction.  BF16 pass (BF16 operands
+// after layer 1, FP32 accumulation): layers 2-4 in k3c_zsweep_bf16, layer 4 with its 3 outputs padded to 16, layer 1
+// with split operands (k3c_zconv1_split).
 //
 // Activations between layers: FP32 [G^3][32], cell-major (z, y, x; x fastest),
 // 32 channels per cell.  Input velocity and output displacement: FP32
