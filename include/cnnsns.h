@@ -212,7 +212,8 @@ typedef struct {
  *   start     int32 [n] output K_p.
  *   cls       int32 [n] output class, or NULL.
  *   logits    FP32 [n][81] output logits, or NULL.
- * Uses a workspace of the mesh (at most 4.4 KB per point, for up to 65,536
+ * Uses a workspace of the mesh (2.2 MiB of prepared weights and at most
+ * 4.4 KB per point, for up to 65,536
  * points at a time), ordered after the previous classification on the mesh
  * like cnnsns_predict.  Asynchronous on `stream` (the first call on a mesh
  * synchronises it once, to build the pooled grid).  n == 0 is a no-op.

@@ -10,8 +10,8 @@
 // of similar length for neighbouring points) a wavefront takes 64 points, one
 // per lane: 20 % faster than chunks of 512 and 7 % faster than 128, the wider
 // grid hiding more of each hop's latency.  Each hop is one 64-byte gather of
-// the current element's record; the geometry is FP64 with no fused
-// multiply-add, exactly as written.
+// the current element's record (in large batches through LDS, launch_mode);
+// the geometry is FP64 with no fused multiply-add, exactly as written.
 #pragma clang fp contract(off)
 
 #include "common.h"
