@@ -40,19 +40,19 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 
 # the source file(s) each benchmark kernel group is built from
 SOURCES = {
-    "cnn_forward_f32": ("cnn.hip", "strip.h"),
-    "cnn_forward_bf16": ("cnn_bf16.hip",),
-    "cnn_forward_fp8": ("cnn_fp8.hip",),
-    "k_locate_plain": ("sns_walk.hip",),
-    "k_locate_cnn": ("sns_walk.hip",),
-    "k_interp": ("sns_walk.hip",),
-    "k_locate_cnn_interp": ("sns_walk.hip",),
-    "k3_locate_plain": ("mesh3d.hip",),
-    "k3_locate_lookup": ("mesh3d.hip",),
-    "k3_locate_cnn": ("mesh3d.hip",),
-    "k3_interp": ("mesh3d.hip",),
-    "cnn3_forward_f32": ("cnn3d.hip",),
-    "cnn3_forward_bf16": ("cnn3d.hip",),
+    "cnn_forward_f32": ("cnn.hip", "strip.h", "cnn_rows.h", "split.h", "lds_copy.h"),
+    "cnn_forward_bf16": ("cnn_bf16.hip", "cnn_strips.h"),
+    "cnn_forward_fp8": ("cnn_fp8.hip", "cnn_strips.h"),
+    "k_locate_plain": ("sns_walk.hip", "xcd_order.h", "lds_copy.h"),
+    "k_locate_cnn": ("sns_walk.hip", "xcd_order.h", "lds_copy.h"),
+    "k_interp": ("sns_walk.hip", "xcd_order.h", "lds_copy.h"),
+    "k_locate_cnn_interp": ("sns_walk.hip", "xcd_order.h", "lds_copy.h"),
+    "k3_locate_plain": ("mesh3d.hip", "xcd_order.h", "lds_copy.h"),
+    "k3_locate_lookup": ("mesh3d.hip", "xcd_order.h", "lds_copy.h"),
+    "k3_locate_cnn": ("mesh3d.hip", "xcd_order.h", "lds_copy.h"),
+    "k3_interp": ("mesh3d.hip", "xcd_order.h", "lds_copy.h"),
+    "cnn3_forward_f32": ("cnn3d.hip", "split.h"),
+    "cnn3_forward_bf16": ("cnn3d.hip", "split.h"),
 }
 
 
