@@ -329,7 +329,7 @@ __global__ __launch_bounds__(kBlock) void k3_locate(const TetRec* __restrict__ r
     char* const my_rec = s_rec[SHARED ? threadIdx.x / 64 : 0];
     const int64_t point = (int64_t)(SHARED ? order.block() : blockIdx.x) * kBlock + threadIdx.x;
     if (!SHARED && point >= n) return;
-    const int64_t idx = point < n ? point : n - 1;  // lanes past the last point: not walked, not written
+    const int64_t idx = !SHARED || point < n ? point : n - 1;  // SHARED lanes past the last point: not walked, not written
     const double3 p{ xp[3 * idx], xp[3 * idx + 1], xp[3 * idx + 2] };
     int32_t K;
     if (MODE == S3_GIVEN) {
@@ -346,10 +346,16 @@ __global__ __launch_bounds__(kBlock) void k3_locate(const TetRec* __restrict__ r
         K = lookup[((int64_t)cell3(q.z, G) * G + cell3(q.y, G)) * G + cell3(q.x, G)];
         if (K < 0) K = (MODE == S3_CNN && start) ? start[idx] : 0;  // a cell with no element
     }
-    bool active = point < n;
+    bool active = !SHARED || point < n;
     int32_t I = 0;
     int fin = CNNSNS_BADSTART;
     if (K < 0 || K >= n_tet) {
+        if (!SHARED) {
+            host[idx] = -1;
+            if (iters) iters[idx] = 0;
+            if (status) status[idx] = CNNSNS_BADSTART;
+            return;
+        }
         K = -1;
         active = false;
     }
@@ -371,8 +377,6 @@ __global__ __launch_bounds__(kBlock) void k3_locate(const TetRec* __restrict__ r
             both(__builtin_amdgcn_mov_dpp(at, 0xff, 0xf, 0xf, true), 3);
             lds_copies_arrived();
             if (!active) continue;
-        } else if (!active) {
-            break;
         }
         I = I + 1;
         double3 v[4];
@@ -384,6 +388,7 @@ __global__ __launch_bounds__(kBlock) void k3_locate(const TetRec* __restrict__ r
         numerators(p, v, o, s);
         if (s[0] >= 0.0 && s[1] >= 0.0 && s[2] >= 0.0 && s[3] >= 0.0) {
             fin = CNNSNS_FOUND;
+            if (!SHARED) break;
             active = false;
             continue;
         }
@@ -402,16 +407,18 @@ __global__ __launch_bounds__(kBlock) void k3_locate(const TetRec* __restrict__ r
         }
         if (m == -1) {
             fin = CNNSNS_OUTSIDE;
+            if (!SHARED) break;
             active = false;
             continue;
         }
         K = m;
         if (I >= max_iter) {
             fin = CNNSNS_MAXITER;
+            if (!SHARED) break;
             active = false;
         }
     }
-    if (point >= n) return;
+    if (SHARED && point >= n) return;
     host[idx] = K;
     if (iters) iters[idx] = I;
     if (status) status[idx] = (uint8_t)fin;
