@@ -599,7 +599,7 @@ void launch_locate3(const cnnsns_mesh3_s& m, int64_t n, const double* xp, const 
         run(k3_locate<S3_CNN, false>, order.blocks);
     else if (!start)
         run(k3_locate<S3_LOOKUP, false>, order.blocks);
-    else if (blocks < kSharedBlocks)
+    else if (blocks < kSharedBlocks || !order.chunk)
         run(k3_locate<S3_GIVEN, false>, order.blocks);
     else
         run(k3_locate<S3_GIVEN, true>, order.grid());
