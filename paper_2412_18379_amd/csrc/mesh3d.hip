@@ -319,7 +319,7 @@ __global__ __launch_bounds__(kBlock) void k3_locate(const TetRec* __restrict__ r
                                                     const double* __restrict__ origin, const float* __restrict__ disp,
                                                     const int32_t* __restrict__ lookup, int32_t G, int32_t max_iter,
                                                     int32_t* __restrict__ host, int32_t* __restrict__ iters,
-                                                    uint8_t* __restrict__ status, XcdOrder order)
+                                                    uint8_t* __restrict__ status, XcdOrder order, double near2)
 {
     // SHARED: records by way of LDS.  In copy k of eight, each eight lanes fetch the record of their lane k, 16 bytes each;
     // a copy lies 65 16-byte places after the one before, so that lanes reading the same part use distinct banks.
@@ -359,39 +359,16 @@ __global__ __launch_bounds__(kBlock) void k3_locate(const TetRec* __restrict__ r
         K = -1;
         active = false;
     }
-    for (;;) {
-        if (SHARED) {
-            if (__ballot(active) == 0) break;
-            const int at = active ? K : 0;
-            const char* part = reinterpret_cast<const char*>(rec) + 16 * (lane & 7);
-            const bool high = lane & 4;
-            auto copy = [&](int e, int k) { lds_copy16(part + (int64_t)e * (int64_t)sizeof(TetRec), my_rec + k * kCopy); };
-            auto both = [&](int b, int k) {  // b: lane k of each quad, in the whole quad
-                const int m = __builtin_amdgcn_mov_dpp(b, 0x141, 0xf, 0xf, true);  // the other quad of the eight
-                copy(high ? m : b, k);
-                copy(high ? b : m, k + 4);
-            };
-            both(__builtin_amdgcn_mov_dpp(at, 0x00, 0xf, 0xf, true), 0);
-            both(__builtin_amdgcn_mov_dpp(at, 0x55, 0xf, 0xf, true), 1);
-            both(__builtin_amdgcn_mov_dpp(at, 0xaa, 0xf, 0xf, true), 2);
-            both(__builtin_amdgcn_mov_dpp(at, 0xff, 0xf, 0xf, true), 3);
-            lds_copies_arrived();
-            if (!active) continue;
-        }
+    // One hop, from the record of element K at `r`: the outcome where the walk ends, else -1.
+    auto hop = [&](const TetRec* r) -> int {
         I = I + 1;
         double3 v[4];
         int32_t nb[4], o;
         uint32_t pos;
-        load_tet(SHARED ? reinterpret_cast<const TetRec*>(my_rec + (lane & 7) * kCopy + (lane >> 3) * (int)sizeof(TetRec)) : rec + K,
-                 0, v, nb, o, pos);
+        load_tet(r, 0, v, nb, o, pos);
         double s[4];
         numerators(p, v, o, s);
-        if (s[0] >= 0.0 && s[1] >= 0.0 && s[2] >= 0.0 && s[3] >= 0.0) {
-            fin = CNNSNS_FOUND;
-            if (!SHARED) break;
-            active = false;
-            continue;
-        }
+        if (s[0] >= 0.0 && s[1] >= 0.0 && s[2] >= 0.0 && s[3] >= 0.0) return CNNSNS_FOUND;
         // eq. (5): the smallest coordinate, ties to the lowest position in the element order
         double sm = s[0];
         uint32_t pm = pos & 0xffu;
@@ -405,18 +382,36 @@ __global__ __launch_bounds__(kBlock) void k3_locate(const TetRec* __restrict__ r
                 m = nb[k];
             }
         }
-        if (m == -1) {
-            fin = CNNSNS_OUTSIDE;
-            if (!SHARED) break;
-            active = false;
-            continue;
-        }
+        if (m == -1) return CNNSNS_OUTSIDE;
         K = m;
-        if (I >= max_iter) {
-            fin = CNNSNS_MAXITER;
-            if (!SHARED) break;
-            active = false;
+        return I >= max_iter ? CNNSNS_MAXITER : -1;
+    };
+    // by way of LDS where the wavefront's points lie in order: most of the 60 lanes with one before them near that one
+    if (SHARED && __popcll(__ballot(point < n && near_lane_before(near2, p.x, p.y, p.z))) >= 40) {
+        const char* part = reinterpret_cast<const char*>(rec) + 16 * (lane & 7);
+        const bool high = lane & 4;
+        while (__ballot(active) != 0) {
+            const int at = active ? K : 0;
+            auto copy = [&](int e, int k) { lds_copy16(part + (int64_t)e * (int64_t)sizeof(TetRec), my_rec + k * kCopy); };
+            auto both = [&](int b, int k) {  // b: lane k of each quad, in the whole quad
+                const int m = __builtin_amdgcn_mov_dpp(b, 0x141, 0xf, 0xf, true);  // the other quad of the eight
+                copy(high ? m : b, k);
+                copy(high ? b : m, k + 4);
+            };
+            both(__builtin_amdgcn_mov_dpp(at, 0x00, 0xf, 0xf, true), 0);
+            both(__builtin_amdgcn_mov_dpp(at, 0x55, 0xf, 0xf, true), 1);
+            both(__builtin_amdgcn_mov_dpp(at, 0xaa, 0xf, 0xf, true), 2);
+            both(__builtin_amdgcn_mov_dpp(at, 0xff, 0xf, 0xf, true), 3);
+            lds_copies_arrived();
+            if (active) {
+                fin = hop(reinterpret_cast<const TetRec*>(my_rec + (lane & 7) * kCopy + (lane >> 3) * (int)sizeof(TetRec)));
+                active = fin < 0;
+            }
         }
+    }
+    while (active) {
+        fin = hop(rec + K);
+        active = fin < 0;
     }
     if (SHARED && point >= n) return;
     host[idx] = K;
@@ -574,12 +569,13 @@ void destroy_mesh3(cnnsns_mesh3 m)
     delete m;
 }
 
-// From given starts with six wavefronts a compute unit or more, records come through LDS and blocks in chunks per XCD: the
-// L1 is what bounds the walk, 512 lookups a hop for 64 records of eight 16-byte loads, one a cycle, where eight lanes
-// that fetch a record together need 128.  With fewer wavefronts a hop's latency counts, which the LDS adds to.  Every
-// vertex, 10 diameters, in us, directly and so: 64k points 92 and 110, 104k 144 and 125, 166k 212 and 162, 373k 395 and
-// 350, 970k 1,005 and 900.  The walks from looked-up starts are short and stay as they are (373k points: 29.5 us in
-// order, 28.4 by XCD).
+// From given starts with six wavefronts a compute unit or more (of 256), blocks go in chunks per XCD, and records come
+// through LDS where a wavefront's points lie in order: the L1 is what bounds the walk, 512 lookups a hop for 64 records of
+// eight 16-byte loads, one a cycle, where eight lanes that fetch a record together need 128.  With fewer wavefronts a
+// hop's latency counts, which the LDS adds to.  Every vertex (n points), 10 diameters, in us, directly and so: 64k
+// points 90 and 108, 104k 148 and 119, 166k 205 and 156, 373k 377 and 344, 970k 995 and 901.  Points in no order share
+// nothing that the LDS could save: 111k points 135 us directly, 146 through LDS, 136 with the wavefront's choice.
+// The walks from looked-up starts are short and stay as they are (373k points: 29.5 us in order, 28.4 by XCD).
 constexpr int64_t kSharedBlocks = 384;
 
 void launch_locate3(const cnnsns_mesh3_s& m, int64_t n, const double* xp, const int32_t* start, const double* origin,
@@ -591,9 +587,11 @@ void launch_locate3(const cnnsns_mesh3_s& m, int64_t n, const double* xp, const 
     const int64_t blocks = (n + kBlock - 1) / kBlock;
     if (blocks > (int64_t)INT32_MAX) fail(CNNSNS_EINVAL, "locate3d: too many points");
     const XcdOrder order((unsigned)blocks, 192);
+    // 16 sides of a cell of the unit cube that holds six tetrahedra
+    const double near2 = 256.0 * std::pow(6.0 / (double)m.n_tet, 2.0 / 3.0);
     auto run = [&](auto kernel, unsigned grid) {
         kernel<<<grid, kBlock, 0, stream>>>(m.rec, m.n_tet, n, xp, start, origin, disp, m.lookup, m.G, max_iter, host, iters,
-                                            status, order);
+                                            status, order, near2);
     };
     if (disp)
         run(k3_locate<S3_CNN, false>, order.blocks);

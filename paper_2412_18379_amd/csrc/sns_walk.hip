@@ -9,7 +9,8 @@
 // faster than 512 and 3.5 % faster than 256).  From given starts (long walks
 // of similar length for neighbouring points) a wavefront takes 64 points, one
 // per lane: 20 % faster than chunks of 512 and 7 % faster than 128, the wider
-// grid hiding more of each hop's latency.  Each hop is one 64-byte gather of
+// grid hiding more of each hop's latency; and a loop of hops alone (1,089 points,
+// 10 diameters: 17.8 us, 24.0 in the loop that also hands out points).  Each hop is one 64-byte gather of
 // the current element's record (in large batches through LDS, launch_mode);
 // the geometry is FP64 with no fused multiply-add, exactly as written.
 #pragma clang fp contract(off)
@@ -24,7 +25,6 @@ namespace {
 constexpr int kWave = 64;
 constexpr int kBlock = 256;
 constexpr int64_t kChunk = 128;      // points per wavefront, looked-up starts (two per lane at least)
-constexpr int64_t kChunkGiven = 64;  // points per wavefront, given starts
 
 __device__ __forceinline__ int32_t cell_of(double x, int32_t G)
 {
@@ -52,7 +52,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WALK == 
                                                    int32_t* __restrict__ host, int32_t* __restrict__ iters,
                                                    uint8_t* __restrict__ status, const int3* __restrict__ tri,
                                                    const double2* __restrict__ nodal, double2* __restrict__ out,
-                                                   XcdOrder order)
+                                                   XcdOrder order, double near2)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const unsigned block = WALK == kInOrder ? blockIdx.x : order.block(), blocks = WALK == kInOrder ? gridDim.x : order.blocks;
@@ -60,7 +60,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WALK == 
     const int64_t wave = ((int64_t)block * kBlock + threadIdx.x) / kWave;
     const int64_t n_waves = (int64_t)blocks * (kBlock / kWave);
     // From the element before movement (long paths, where neighbouring points share elements)
-    // a wave owns kChunkGiven slots: slot v is point wave kChunkGiven + v, a contiguous chunk.
+    // a wave takes kWave consecutive points, a lane one of them.
     // From a looked-up start (short paths, whose rare long ones cluster at the two ends of the
     // point order, the domain boundary) a wave owns kChunk slots, R = kChunk / 64 runs of 64
     // consecutive points strided across all points, so the long walks of one region spread over
@@ -68,16 +68,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WALK == 
     // n_waves - 1 - wave for odd u, so both ends of the point order fall to the first waves,
     // which walk them first (runs in the order 0, R - 1, 1, R - 2, ...).
     auto point_of = [&](int64_t v) -> int64_t {
-        if (MODE == START_GIVEN) return wave * kChunkGiven + v;
         const int k = (int)(v >> 6);
         const int u = (k & 1) ? (int)(kChunk / 64) - 1 - (k >> 1) : (k >> 1);
         const int64_t b = (u & 1) ? n_waves - 1 - wave : wave;
         return ((b + u * n_waves) << 6) + (v & (kWave - 1));
     };
     int64_t next = 0;  // wave-uniform: next unstarted slot
-    const int64_t n_slots =
-        MODE == START_GIVEN ? (n - wave * kChunkGiven < kChunkGiven ? n - wave * kChunkGiven : kChunkGiven) : kChunk;
-    if (MODE == START_GIVEN && n_slots <= 0) return;
+    const int64_t n_slots = kChunk;
+    if (MODE == START_GIVEN && wave * kWave >= n) return;
 
     // Start elements that depend on a lookup (CNN-SNS, ASG) are computed for the whole chunk
     // first, eight independent load chains per lane, and kept in LDS: a lane that takes a new
@@ -154,119 +152,136 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WALK == 
     int fin_given = -1;          // given starts: the lane's outcome, written after the loop
     double lam_given[3] = { 0.0, 0.0, 0.0 };
 
-    for (;;) {
-        // hand unstarted points of the chunk to idle lanes
-        const uint64_t idle = __ballot(!active);
-        if (idle != 0 && next < n_slots) {
-            const uint32_t lo = (uint32_t)idle, hi = (uint32_t)(idle >> 32);
-            const int rank = (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
-            if (!active && next + rank < n_slots) {
-                const int64_t v = next + rank;
-                idx = point_of(v);
-                slot = v;
-                if (idx < n) {
-                    const double2 p = xp[idx];
-                    px = p.x;
-                    py = p.y;
-                    K = MODE == START_GIVEN ? start[idx] : my_start[v];
-                    I = 0;
-                    if (K < 0 || K >= n_tri) {  // no element: host -1, path 0 (and a NaN interpolant)
-                        if (MODE == START_GIVEN) {
-                            fin_given = CNNSNS_BADSTART;
-                            K = -1;
-                        } else {
+    // One hop, from the record of element K at `r`: the outcome where the walk ends, else -1.
+    auto hop = [&](const void* r) -> int {
+        I = I + 1;
+        const double2* r2 = static_cast<const double2*>(r);
+        const double2 A = r2[0], B = r2[1], C = r2[2];
+        const int4 nb = static_cast<const int4*>(r)[3];
+        // barycentric numerators s_j = |S_j| (Sec. 2.2), vertex j's column replaced by x_p
+        const double adx = A.x - px, ady = A.y - py;
+        const double bdx = B.x - px, bdy = B.y - py;
+        const double cdx = C.x - px, cdy = C.y - py;
+        const double s0 = bdx * cdy - bdy * cdx;
+        const double s1 = cdx * ady - cdy * adx;
+        const double s2 = adx * bdy - ady * bdx;
+        // the neighbour ids arrive with the coordinates (one 64-byte line): keep their load beside
+        // the others, not sunk behind the containment test as a second dependent access
+        asm volatile("" : : "v"(nb.x), "v"(nb.y), "v"(nb.z));
+        int fin = -1;
+        if (s0 >= 0.0 && s1 >= 0.0 && s2 >= 0.0) {
+            fin = CNNSNS_FOUND;  // closed containment: all coordinates >= 0
+        } else {
+            // eq. (5): smallest coordinate, ties to the lowest index
+            int32_t m = nb.x;
+            double smin = s0;
+            if (s1 < smin) { smin = s1; m = nb.y; }
+            if (s2 < smin) { m = nb.z; }
+            if (m == -1) {
+                fin = CNNSNS_OUTSIDE;
+            } else {
+                K = m;
+                if (I >= max_iter) fin = CNNSNS_MAXITER;
+            }
+        }
+        if (fin >= 0) {
+            double lam[3] = { 0.0, 0.0, 0.0 };
+            if (INTERP) {  // barycentric coordinates s_j / |S_0| of x_p in the host
+                double2 a = A, b = B, c = C;
+                double t0 = s0, t1 = s1, t2 = s2;
+                if (fin == CNNSNS_MAXITER) {  // the host is the element just moved to
+                    const double2* q2 = reinterpret_cast<const double2*>(rec + K);
+                    a = q2[0];
+                    b = q2[1];
+                    c = q2[2];
+                    const double ax_ = a.x - px, ay_ = a.y - py, bx_ = b.x - px, by_ = b.y - py;
+                    const double cx_ = c.x - px, cy_ = c.y - py;
+                    t0 = bx_ * cy_ - by_ * cx_;
+                    t1 = cx_ * ay_ - cy_ * ax_;
+                    t2 = ax_ * by_ - ay_ * bx_;
+                }
+                const double area2 = (b.x - a.x) * (c.y - a.y) - (b.y - a.y) * (c.x - a.x);
+                lam[0] = t0 / area2;
+                lam[1] = t1 / area2;
+                lam[2] = t2 / area2;
+            }
+            if (MODE == START_GIVEN) {
+                fin_given = fin;
+                if (INTERP)
+                    for (int j = 0; j < 3; ++j) lam_given[j] = lam[j];
+            } else {
+                my_start[slot] = K;
+                s_iters[wslot][slot] = I;
+                s_status[wslot][slot] = (uint8_t)fin;
+                if (INTERP)
+                    for (int j = 0; j < 3; ++j) s_lam[wslot][j][slot] = lam[j];
+            }
+        }
+        return fin;
+    };
+    if constexpr (MODE == START_GIVEN) {  // a lane walks one point
+        idx = wave * kWave + lane;
+        if (idx < n) {
+            const double2 p = xp[idx];
+            px = p.x;
+            py = p.y;
+            K = start[idx];
+            active = K >= 0 && K < n_tri;
+            if (!active) {
+                fin_given = CNNSNS_BADSTART;
+                K = -1;
+            }
+        }
+        // by way of LDS where the wavefront's points lie in order: most of the 60 lanes with one before them near that one
+        if (SHARED && __popcll(__ballot(idx < n && near_lane_before(near2, px, py))) >= 40) {
+            const char* quarter = reinterpret_cast<const char*>(rec) + 16 * (lane & 3);
+            const char* const r = my_rec + (lane & 3) * kCopy + (lane >> 2) * (int)sizeof(ElemRec);
+            while (__ballot(active) != 0) {
+                const int at = active ? K : 0;
+                auto copy = [&](int e, int k) { lds_copy16(quarter + (int64_t)e * (int64_t)sizeof(ElemRec), my_rec + k * kCopy); };
+                copy(__builtin_amdgcn_mov_dpp(at, 0x00, 0xf, 0xf, true), 0);  // lane 0 of each quad to all four
+                copy(__builtin_amdgcn_mov_dpp(at, 0x55, 0xf, 0xf, true), 1);
+                copy(__builtin_amdgcn_mov_dpp(at, 0xaa, 0xf, 0xf, true), 2);
+                copy(__builtin_amdgcn_mov_dpp(at, 0xff, 0xf, 0xf, true), 3);
+                lds_copies_arrived();
+                if (active && hop(r) >= 0) active = false;
+            }
+        }
+        while (active)
+            if (hop(rec + K) >= 0) active = false;
+    } else {
+        for (;;) {
+            // hand unstarted points of the chunk to idle lanes
+            const uint64_t idle = __ballot(!active);
+            if (idle != 0 && next < n_slots) {
+                const uint32_t lo = (uint32_t)idle, hi = (uint32_t)(idle >> 32);
+                const int rank = (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+                if (!active && next + rank < n_slots) {
+                    const int64_t v = next + rank;
+                    idx = point_of(v);
+                    slot = v;
+                    if (idx < n) {
+                        const double2 p = xp[idx];
+                        px = p.x;
+                        py = p.y;
+                        K = my_start[v];
+                        I = 0;
+                        if (K < 0 || K >= n_tri) {  // no element: host -1, path 0 (and a NaN interpolant)
                             my_start[v] = -1;
                             s_iters[wslot][v] = 0;
                             s_status[wslot][v] = CNNSNS_BADSTART;
+                        } else {
+                            active = true;
                         }
-                    } else {
-                        active = true;
                     }
                 }
+                next += __popcll(idle);
             }
-            next += __popcll(idle);
-        }
-        if (__ballot(active) == 0) {
-            if (next >= n_slots) break;
-            continue;
-        }
-        if (SHARED) {
-            const int at = active ? K : 0;
-            const char* quarter = reinterpret_cast<const char*>(rec) + 16 * (lane & 3);
-            auto copy = [&](int e, int k) { lds_copy16(quarter + (int64_t)e * (int64_t)sizeof(ElemRec), my_rec + k * kCopy); };
-            copy(__builtin_amdgcn_mov_dpp(at, 0x00, 0xf, 0xf, true), 0);  // lane 0 of each quad to all four
-            copy(__builtin_amdgcn_mov_dpp(at, 0x55, 0xf, 0xf, true), 1);
-            copy(__builtin_amdgcn_mov_dpp(at, 0xaa, 0xf, 0xf, true), 2);
-            copy(__builtin_amdgcn_mov_dpp(at, 0xff, 0xf, 0xf, true), 3);
-            lds_copies_arrived();
-        }
-        if (active) {
-            I = I + 1;
-            const char* const r = SHARED ? my_rec + (lane & 3) * kCopy + (lane >> 2) * (int)sizeof(ElemRec)
-                                         : reinterpret_cast<const char*>(rec + K);
-            const double2* r2 = reinterpret_cast<const double2*>(r);
-            const double2 A = r2[0], B = r2[1], C = r2[2];
-            const int4 nb = reinterpret_cast<const int4*>(r)[3];
-            // barycentric numerators s_j = |S_j| (Sec. 2.2), vertex j's column replaced by x_p
-            const double adx = A.x - px, ady = A.y - py;
-            const double bdx = B.x - px, bdy = B.y - py;
-            const double cdx = C.x - px, cdy = C.y - py;
-            const double s0 = bdx * cdy - bdy * cdx;
-            const double s1 = cdx * ady - cdy * adx;
-            const double s2 = adx * bdy - ady * bdx;
-            // the neighbour ids arrive with the coordinates (one 64-byte line): keep their load beside
-            // the others, not sunk behind the containment test as a second dependent access
-            asm volatile("" : : "v"(nb.x), "v"(nb.y), "v"(nb.z));
-            int fin = -1;
-            if (s0 >= 0.0 && s1 >= 0.0 && s2 >= 0.0) {
-                fin = CNNSNS_FOUND;  // closed containment: all coordinates >= 0
-            } else {
-                // eq. (5): smallest coordinate, ties to the lowest index
-                int32_t m = nb.x;
-                double smin = s0;
-                if (s1 < smin) { smin = s1; m = nb.y; }
-                if (s2 < smin) { m = nb.z; }
-                if (m == -1) {
-                    fin = CNNSNS_OUTSIDE;
-                } else {
-                    K = m;
-                    if (I >= max_iter) fin = CNNSNS_MAXITER;
-                }
+            if (__ballot(active) == 0) {
+                if (next >= n_slots) break;
+                continue;
             }
-            if (fin >= 0) {
-                double lam[3] = { 0.0, 0.0, 0.0 };
-                if (INTERP) {  // barycentric coordinates s_j / |S_0| of x_p in the host
-                    double2 a = A, b = B, c = C;
-                    double t0 = s0, t1 = s1, t2 = s2;
-                    if (fin == CNNSNS_MAXITER) {  // the host is the element just moved to
-                        const double2* q2 = reinterpret_cast<const double2*>(rec + K);
-                        a = q2[0];
-                        b = q2[1];
-                        c = q2[2];
-                        const double ax_ = a.x - px, ay_ = a.y - py, bx_ = b.x - px, by_ = b.y - py;
-                        const double cx_ = c.x - px, cy_ = c.y - py;
-                        t0 = bx_ * cy_ - by_ * cx_;
-                        t1 = cx_ * ay_ - cy_ * ax_;
-                        t2 = ax_ * by_ - ay_ * bx_;
-                    }
-                    const double area2 = (b.x - a.x) * (c.y - a.y) - (b.y - a.y) * (c.x - a.x);
-                    lam[0] = t0 / area2;
-                    lam[1] = t1 / area2;
-                    lam[2] = t2 / area2;
-                }
-                if (MODE == START_GIVEN) {
-                    fin_given = fin;
-                    if (INTERP)
-                        for (int j = 0; j < 3; ++j) lam_given[j] = lam[j];
-                } else {
-                    my_start[slot] = K;
-                    s_iters[wslot][slot] = I;
-                    s_status[wslot][slot] = (uint8_t)fin;
-                    if (INTERP)
-                        for (int j = 0; j < 3; ++j) s_lam[wslot][j][slot] = lam[j];
-                }
-                active = false;
-            }
+            if (active && hop(rec + K) >= 0) active = false;
         }
     }
     // the interpolant at x_p: sum_j lambda_j nodal[node j] over the host's nodes in counter-clockwise
@@ -279,12 +294,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WALK == 
     };
     // the wave's results, coalesced
     if (MODE == START_GIVEN) {
-        const int64_t i = wave * kChunkGiven + lane;
-        if (fin_given >= 0 && i < n) {
-            host[i] = K;
-            if (iters) iters[i] = fin_given == CNNSNS_BADSTART ? 0 : I;
-            if (status) status[i] = (uint8_t)fin_given;
-            if (INTERP) out[i] = interpolant(K, lam_given);
+        if (idx < n) {
+            host[idx] = K;
+            if (iters) iters[idx] = I;
+            if (status) status[idx] = (uint8_t)fin_given;
+            if (INTERP) out[idx] = interpolant(K, lam_given);
         }
     } else {
         __builtin_amdgcn_wave_barrier();
@@ -353,15 +367,22 @@ void launch_interp(const cnnsns_mesh_s& m, int64_t n, const double* xp, const in
     hip_check(hipGetLastError(), "interpolate launch");
 }
 
-// In order of id below 64 blocks (a walk of 1,922 points: 9.4 us, 9.7 with the reordering's few instructions); by XCD from
-// there; and from given starts with 24 wavefronts a compute unit or more also through LDS.  There the L1 is what bounds
-// the walk: it looks up one line a cycle, 256 a hop for 64 records of four 16-byte loads, where four lanes that
-// fetch a record together need 64.  With fewer wavefronts a hop's latency counts, which the LDS adds to.  Every centroid,
-// 20 diameters, in us, in order, by XCD and through LDS: 250k points 76, 65 and 71, 500k 134, 119 and 98, 1M 294, 283
-// and 235; CNN starts, in order and by XCD: 0.5M 20.3 and 18.0, 1M 36.7 and 33.2, 2M 77.2 and 76.4.
-// Looked-up starts go in order again past 6,144 blocks, whose short walks have little left to share: 4M points 168.6
-// and 169.5, ASG starts 139 and 140.
-constexpr int64_t kSharedWaves = 6144;
+// In order of id up to 64 blocks, by XCD from there, and from given starts with 10 wavefronts a compute unit or more (of
+// 256) in the form that takes records through LDS where a wavefront's points lie in order.  There the L1 bounds
+// the walk: it looks up one line a cycle, 256 a hop for 64 records of four 16-byte loads, where four lanes that fetch a
+// record together need 64.  With fewer wavefronts a hop's latency counts, which the LDS adds to.  Walks of every node (n
+// points), 20 diameters, in us, in order, by XCD and through LDS:
+//     n      16k    20k    66k    125k   160k   250k   503k   1M     4M     8M
+//     order  35.3   36.1   55.5   66.4   87.3   124    217    383    1528   3085
+//     XCD    35.2   34.8   49.5   54.4   77.4   113    175    357    1511   2996
+//     LDS    35.3   52.0   52.3   60.3   71.7   89     154    298    1223   2569
+// (8M points, 160 diameters, whose paths have left their neighbours: 19.0, 18.9 and 19.7 ms.)  Points in no order share
+// nothing that the LDS could save: 503k points, 10 diameters, 168 us with every record from memory, 187 with all through
+// LDS, 165 with the wavefront's choice (in order: 130, 90 and 87).
+// CNN starts, in order and by XCD: 0.5M 20.3 and 18.0, 1M 36.7 and 33.2, 2M 77.2 and 76.4.  Looked-up starts go in
+// order again past 6,144 blocks, whose short walks have little left to share: 4M points 168.6 and 169.5, ASG starts 139
+// and 140.
+constexpr int64_t kSharedWaves = 2560;
 constexpr unsigned kOrderedBlocks = 6144;
 
 template <int MODE, bool INTERP>
@@ -370,11 +391,12 @@ static void launch_mode(const cnnsns_mesh_s& m, int64_t n, const double2* xp2, c
                         uint8_t* status, const double* nodal, double* out, unsigned blocks, hipStream_t stream)
 {
     const XcdOrder order(MODE == START_GIVEN || blocks <= kOrderedBlocks ? blocks : 0, MODE == START_GIVEN ? 128 : 32);
+    const double near2 = 256.0 * m.mean_diam * m.mean_diam;  // 16 diameters
     auto run = [&](auto kernel) {
         kernel<<<order.chunk ? order.grid() : blocks, kBlock, 0, stream>>>(m.rec, m.n_tri, n, xp2, start, or2, disp, m.lookup, m.G, max_iter, host,
                                                     iters, status, reinterpret_cast<const int3*>(m.tri),
                                                     reinterpret_cast<const double2*>(nodal), reinterpret_cast<double2*>(out),
-                                                    order);
+                                                    order, near2);
     };
     if (order.chunk == 0)
         run(k_locate<MODE, INTERP, kInOrder>);
@@ -390,7 +412,7 @@ void launch_locate(const cnnsns_mesh_s& m, int64_t n, const double* xp, const in
 {
     if (n == 0) return;
     if (max_iter <= 0) max_iter = 1 << 20;
-    const int64_t chunk = (!disp && start) ? kChunkGiven : kChunk;
+    const int64_t chunk = (!disp && start) ? kWave : kChunk;
     const int64_t waves = (n + chunk - 1) / chunk;
     const int64_t blocks = (waves * kWave + kBlock - 1) / kBlock;
     if (blocks > (int64_t)INT32_MAX) fail(CNNSNS_EINVAL, "locate: too many points");

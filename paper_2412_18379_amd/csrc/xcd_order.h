@@ -8,6 +8,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstdint>
+
 namespace cnnsns {
 
 struct XcdOrder {
@@ -31,5 +33,21 @@ struct XcdOrder {
     }
     __device__ __forceinline__ unsigned block() const { return block(blockIdx.x); }
 };
+
+// x of the lane before in a row of 16 (0 for the first)
+__device__ __forceinline__ double lane_before(double x)
+{
+    const uint64_t b = __double_as_longlong(x);
+    const uint32_t lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)b, 0x111, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), 0x111, 0xf, 0xf, true);
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// Whether this lane's point lies within sqrt(near2) of the lane before's, in a row of 16 lanes.
+template <class... X>
+__device__ __forceinline__ bool near_lane_before(double near2, X... x)
+{
+    return (((x - lane_before(x)) * (x - lane_before(x))) + ...) <= near2;
+}
 
 }  // namespace cnnsns
