@@ -132,6 +132,9 @@ int cnnsns_destroy_mesh(cnnsns_mesh m);
  * CNN forward pass over the mesh's G x G overlay (the prediction step of
  * Alg. 2, in the displacement-regression form described above):
  *   vel   DEVICE FP32 [2][G][G], (u, v) at the cell centres, row = y index.
+ *         One that is infinite or not a number leaves the displacements
+ *         within four cells of it undefined, and (but for an infinite one in
+ *         FP8, which takes part in the scale) no others.
  *   w     the weights (device pointers, see cnnsns_cnn).
  *   precision  CNNSNS_F32, CNNSNS_BF16 or CNNSNS_FP8E4M3.
  *   disp  DEVICE FP32 [2][G][G] output (caller-owned): predicted (dx, dy).

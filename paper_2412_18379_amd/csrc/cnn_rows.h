@@ -413,7 +413,7 @@ static __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu
         if (t < VPX) {
             const bool in = (unsigned)v < (unsigned)G && (unsigned)(x0 - 2 + t) < (unsigned)G;
             uint32_t h, m, l;
-            split_pair(in ? pu : 0.f, in ? pv : 0.f, h, m, l);
+            split_pair_any(in ? pu : 0.f, in ? pv : 0.f, h, m, l);
             s_vel[v & 3][0][t] = h;
             s_vel[v & 3][1][t] = m;
             s_vel[v & 3][2][t] = l;

@@ -39,7 +39,10 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b)
     return __builtin_bit_cast(uint32_t, p);
 }
 
-// (a, b) as three packed BF16 pairs; the remainders are exact FP32 subtractions.
+constexpr uint32_t kBf16Top = 0x7f7f0000u;  // BF16's largest finite value, 3.39e38, as FP32
+
+// (a, b) as three packed BF16 pairs; the remainders are exact FP32 subtractions.  For values up to 3.39e38: an activation
+// beyond is within 0.4 % of FP32's own end.
 __device__ __forceinline__ void split_pair(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l)
 {
     h = bf16_pair(a, b);
@@ -49,6 +52,18 @@ __device__ __forceinline__ void split_pair(float a, float b, uint32_t& h, uint32
     a -= __uint_as_float(m << 16);
     b -= __uint_as_float(m & 0xffff0000u);
     l = bf16_pair(a, b);
+}
+
+// The same for any finite values, as the caller's are: those between BF16's largest value and FP32's, which rounding would
+// take to infinity, are BF16's largest value and a remainder.
+__device__ __forceinline__ void split_pair_any(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l)
+{
+    const float top = __uint_as_float(kBf16Top);
+    h = bf16_pair(__builtin_amdgcn_fmed3f(a, -top, top), __builtin_amdgcn_fmed3f(b, -top, top));
+    a -= __uint_as_float(h << 16);
+    b -= __uint_as_float(h & 0xffff0000u);
+    m = bf16_pair(a, b);
+    l = bf16_pair(a - __uint_as_float(m << 16), b - __uint_as_float(m & 0xffff0000u));
 }
 
 __device__ __forceinline__ Split8 split8(const v4f& a, const v4f& b)
@@ -69,7 +84,8 @@ __device__ __forceinline__ Split8 split8(const v4f& a, const v4f& b)
 // One weight, prepared in FP64, as the `part`-th of its three BF16 values.
 __device__ __forceinline__ __bf16 split_part(double x, int part)
 {
-    const __bf16 h = (__bf16)(float)x;
+    const float top = __uint_as_float(kBf16Top);
+    const __bf16 h = (__bf16)__builtin_amdgcn_fmed3f((float)x, -top, top);
     if (part == 0) return h;
     const double r = x - (double)(float)h;
     const __bf16 m = (__bf16)(float)r;
