@@ -226,17 +226,16 @@ __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(2, 2)
     }
 }
 
-// Layer 1 (3 -> 32) as a z-sweep on the matrix cores in FP32 (both passes; the BF16 pass rounds
-// its output): the velocity's three planes in LDS as (u, v, w, 0) per cell, one
-// v_mfma_f32_16x16x4f32 per tap and 16 output channels with K = the three components and a zero,
-// the weights (one float per lane, tap and block of 16 output channels) held in registers.
+// Layer 1 of the FP32 pass (3 -> 32) as a z-sweep on the FP32 matrix instruction: the velocity's
+// three planes in LDS as (u, v, w, 0) per cell, one v_mfma_f32_16x16x4f32 per tap and 16 output
+// channels with K = the three components and a zero, the weights (one float per lane, tap and
+// block of 16 output channels) held in registers.
 constexpr int Z1CS = 4;  // floats per slab cell
 
 constexpr int kZ1Threads = 1024;  // one 16-cell M-block per wavefront
-template <class T>
 __global__ __launch_bounds__(kZ1Threads) void k3c_zconv1(int32_t G, int zp, const float* __restrict__ vel,
                                                         const float* __restrict__ w, const float* __restrict__ bias,
-                                                        T* __restrict__ out)
+                                                        float* __restrict__ out)
 {
     constexpr int NCELL = ZSY * ZSX;
     static_assert(NCELL <= kZ1Threads && ZY * ZX == (kZ1Threads / 64) * 16, "one slab cell per thread");
@@ -296,16 +295,11 @@ __global__ __launch_bounds__(kZ1Threads) void k3c_zconv1(int32_t G, int zp, cons
         }
         const int gy = ty0 + r, gx = tx0 + 16 * h + col;
         if (gy < G && gx < G) {
-            T* dst = out + ((int64_t)z * GG + (int64_t)gy * G + gx) * C + 4 * grp;
+            float* dst = out + ((int64_t)z * GG + (int64_t)gy * G + gx) * C + 4 * grp;
             const v4f v0{ fmaxf(acc0.x, 0.f), fmaxf(acc0.y, 0.f), fmaxf(acc0.z, 0.f), fmaxf(acc0.w, 0.f) };
             const v4f v1{ fmaxf(acc1.x, 0.f), fmaxf(acc1.y, 0.f), fmaxf(acc1.z, 0.f), fmaxf(acc1.w, 0.f) };
-            if constexpr (sizeof(T) == 4) {
-                *reinterpret_cast<v4f*>(dst) = v0;
-                *reinterpret_cast<v4f*>(dst + 16) = v1;
-            } else {
-                *reinterpret_cast<bf16x4*>(dst) = __builtin_convertvector(v0, bf16x4);
-                *reinterpret_cast<bf16x4*>(dst + 16) = __builtin_convertvector(v1, bf16x4);
-            }
+            *reinterpret_cast<v4f*>(dst) = v0;
+            *reinterpret_cast<v4f*>(dst + 16) = v1;
         }
         __syncthreads();
         if (z + 2 < z1 + 1) stash(z + 2);
@@ -841,7 +835,7 @@ void run_predict3(cnnsns_mesh3_s& m, const float* vel, const cnnsns_cnn& w, int3
     } else {
         v4f* w4f = reinterpret_cast<v4f*>(wb3 + NWS);
         k3c_prep_f32<<<(kPrepF32 + kBlock - 1) / kBlock, kBlock, 0, stream>>>(w.w[1], w.w[2], w.w[3], wb2, wb3, w4f);
-        k3c_zconv1<float><<<(unsigned)zblocks, kZ1Threads, 0, stream>>>(G, zp, vel, w.w[0], w.b[0], act0);
+        k3c_zconv1<<<(unsigned)zblocks, kZ1Threads, 0, stream>>>(G, zp, vel, w.w[0], w.b[0], act0);
         const int zp2 = z_planes(G, 2 * ztiles, (int)grid);
         const dim3 g2((unsigned)(ztiles * ((G + zp2 - 1) / zp2)), 2);
         k3c_zsplit_f32<<<g2, kZThreads, 0, stream>>>(G, zp2, act0, wb2, w.b[1], act1);
