@@ -1009,8 +1009,8 @@ def main():
                         "achieved": round(2.0 * useful_macs / (pred_ms.mean() / 1e3) / 1e12, 3),
                         "frac": round(2.0 * useful_macs / (pred_ms.mean() / 1e3) / 1e12 / cnn_peak, 4),
                         "note": "the products the method needs: " + (
-                            "Winograd F(2x2,3x3) for conv2/conv3, direct for conv1/conv4" if precision == "f32"
-                            else "direct convolution")},
+                            ("F(2,3) along the rows" if rows else "Winograd F(2x2,3x3)") +
+                            " for conv2/conv3, direct for conv1/conv4" if precision == "f32" else "direct convolution")},
         "direct_conv_equivalent": {"macs_per_cell": CNN_MACS_PER_PIXEL, "achieved": round(cnn_tf, 3),
                                    "note": "2 x 19584 MAC x G^2 over the pass time; exceeds the matrix "
                                            "cores' work when conv2/conv3 run as Winograd"},

@@ -202,7 +202,9 @@ typedef struct {
  * take the nearest cell's value: the padding layer), as G (cell value - x_p)
  * in two channels, and x_p's offset in its own cell, x_p G - (cell + 1/2),
  * both formed in FP64 and rounded to FP32; the network itself runs in FP32
- * (convolutions and the fully connected layers on the matrix cores).  The
+ * (convolutions and the fully connected layers on the matrix cores, conv2 and
+ * the layers of 256 and 512 inputs with every operand as three BF16 values
+ * that add up to it).  The
  * class is the argmax of the 81 logits (the softmax of eq. 7 does not change
  * it; ties go to the lowest class); class (dy + 4) 9 + (dx + 4) is the window
  * cell at offset (dx, dy) from the cell of x_p, clamped to the grid, and the
@@ -330,10 +332,13 @@ int cnnsns_destroy_mesh3d(cnnsns_mesh3 m);
  *   w     weights as in cnnsns_predict, with 3 x 3 x 3 kernels: w[0] FP32
  *         [32][3][3][3][3], w[1], w[2] [32][32][3][3][3], w[3] [3][32][3][3][3]
  *         (OIDHW); b[0..2] [32], b[3] [3].
- *   precision  CNNSNS_F32, or CNNSNS_BF16: layers 2 and 3 with BF16 weights
- *              and activations (rounded to nearest even) on the matrix cores,
- *              FP32 accumulation; layer 1 writes BF16 activations and layer 4
- *              reads them, both computing in FP32.  CNNSNS_FP8E4M3: EINVAL.
+ *   precision  CNNSNS_F32 (layers 2 and 3 with every operand as three BF16
+ *              values that add up to it), or CNNSNS_BF16: layers 2 to 4 with
+ *              BF16 weights and activations (rounded to nearest even) on the
+ *              matrix cores, FP32 accumulation; layer 1 with velocities and
+ *              weights as two BF16 values each, within about 2^-16 of each
+ *              product, and its result rounded to BF16.  CNNSNS_FP8E4M3:
+ *              EINVAL.
  *   disp  FP32 [3][G][G][G] out: the predicted displacement per cell.
  * Uses a workspace of the mesh (2 G^3 x 32 FP32 activations plus 342 KiB),
  * allocated on the first call; a pass is ordered on the device after the

@@ -134,7 +134,7 @@ __global__ void k_pool_mean(int32_t G, const ElemRec* __restrict__ rec, const in
 //
 // What bounds it: matrix instructions (30 of 32 cycles and 120 of 16 a particle) and vector instructions, which add
 // up on a SIMD (cnn_rows.h).  With conv2 on the FP32 instruction over 96 cells, each of its accumulators written back
-// for the pooling, 65,536 particles took 364 us.
+// for the pooling, 65,536 particles took 364 us; now 150.  At three wavefronts per SIMD two registers still spill.
 constexpr int kMThreads = 768;
 constexpr int kMW = kW + 1;              // conv2's input: the window with a border of one, less the last row and column
 constexpr int kMPart = kMW * kMW * 2;    // bf16x8 of one part: two chunks of eight channels a cell

@@ -723,9 +723,12 @@ unsigned cnn_persistent_grid()
 
 // Which form of the FP32 pass runs.  A row block pays for its weights and halo rows, three to five rows'
 // worth, so the row form loses where its segments are a few rows long; below that, at one row a segment,
-// the tile form's single tile for a part of the compute units takes longer.  Kernels of a pass in us, tile and
-// row form: G = 33: 40.8 and 33.1, 128: 41.8 and 36.2, 140: 42 and 46, 256: 44 and 53, 384: 74 and 80, 520: 106 and
-// 105, 576: 121 and 112, 700: 152 and 136, 832: 196 and 178, 1024: 283 and 219, 1531: 583 and 470.
+// the tile form's single tile for a part of the compute units takes longer.  Repeated calls in us:
+//     G     33    128   129   200   256   320   384   450   500   512   520   576   700   832   1024  1531  4096
+//     tile  43.8  44.4  44.6  44.7  45.2  46.1  73.3  74.7  88.9  90.2  101   116   143   184   266   555   3666
+//     row   36.0  38.2  47.0  49.7  51.7  64.4  74.8  80.4  81.6  81.6  99    102   122   162   192   397   2533
+// The upper line lies at 512 and not at about 470, where the two cross: at 512 the row form's workspace is larger than
+// the array of cnnsns_predict_noalloc, which takes G up to 512 and gives the same results.
 static bool rows_form(int32_t G)
 {
     return G <= 128 || G > 512;

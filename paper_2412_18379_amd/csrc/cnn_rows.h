@@ -23,12 +23,12 @@
 // instructions on operands split into three BF16 values each (split.h), with
 // FP32's precision.
 //
-// What bounds it (G = 4096): a wavefront's row is 164 matrix instructions (16.5 cycles each) and about 650
-// vector instructions (3 cycles), and on one SIMD the two add up: two wavefronts that mix them take 14 + 3 n
-// cycles per matrix instruction with n vector instructions, measured.  That sum is 85% of a step.  The
-// other splits of the work, whole pass: the tile form (FP32 matrix instruction, F(2x2, 3x3), cnn.hip)
-// 3.67 ms; this one 2.67; direct convolution on operands split where they enter LDS (216 matrix
-// instructions a row, 400 vector ones) 3.03.  F(2x2, 3x3) on split operands has the same sum as
+// What bounds it (G = 4096): a wavefront's row is 164 matrix instructions (168 in the second kernel; 16.5 cycles each)
+// and about 600 vector instructions (690; 3 cycles), and on one SIMD the two add up: two wavefronts that mix them
+// take 14 + 3 n cycles per matrix instruction with n vector instructions, measured.  That sum is three quarters of
+// the pass, 2.50 ms in repeated calls.  The other splits of the work: the tile form (FP32 matrix instruction,
+// F(2x2, 3x3), cnn.hip) 3.67 ms; direct convolution on operands split where they enter LDS (216 matrix
+// instructions a row, 400 vector ones) 3.03, when this form took 2.67.  F(2x2, 3x3) on split operands has the same sum as
 // F(2,3): a third fewer matrix instructions, but it splits four transformed values per input instead of two,
 // and its 96 KiB of weights do not fit in LDS beside two rows of 258 pixels.
 #pragma once

@@ -15,9 +15,9 @@
 //
 // What bounds it: matrix instructions, 160 per SIMD and step, 2,640 cycles of about 3,900; the rest is the two
 // wavefronts' turns at operand reads, ReLU and barrier.  Against 14 x 30 tiles with their halo recomputed in every layer
-// (38% more matrix instructions, five barriers a tile), the kernel in us, before and now, in BF16: G = 64: 11.5 and
-// 9.2, 256: 12.3 and 12.5, 512: 28 and 21, 1024: 84 and 47, 4096: 974 and 550; in FP8 (with its
-// scales' chain): 64: 12.7 and 12.1, 512: 30 and 24, 1024: 88 and 51, 4096: 1015 and 550.
+// (38% more matrix instructions, five barriers a tile), repeated calls of the whole pass in us, before and now, in BF16:
+// G = 64: 19.0 and 17.2, 256: 19.1 and 18.9, 512: 32.8 and 25.6, 1024: 81 and 48, 4096: 933 and 483; in FP8: 64: 34.8
+// and 20.1, 256: 37.7 and 22.1, 512: 56 and 29, 1024: 110 and 53, 4096: 1082 and 520.
 #pragma once
 
 #include <hip/hip_runtime.h>
