@@ -33,6 +33,7 @@ import csv
 import hashlib
 import json
 import os
+import re
 import sys
 from collections import defaultdict
 
@@ -66,6 +67,13 @@ def source_sha(*names):
 
 def _short(name: str, width: int = 90) -> str:
     """Kernel name without its argument list (and cut to width characters)."""
+    if name.startswith("_ZN"):  # left mangled where an argument's type is BF16: the nested names
+        parts, k = [], 3
+        while m := re.match(r"\d+", name[k:]):
+            k += m.end()
+            parts.append(name[k:k + int(m[0])])
+            k += int(m[0])
+        name = "::".join(p for p in parts if p != "_GLOBAL__N_1")
     name = name.replace("(anonymous namespace)::", "").replace("void ", "")
     depth, out = 0, []
     for ch in name:
