@@ -379,9 +379,10 @@ void launch_interp(const cnnsns_mesh_s& m, int64_t n, const double* xp, const in
 // (8M points, 160 diameters, whose paths have left their neighbours: 19.0, 18.9 and 19.7 ms.)  Points in no order share
 // nothing that the LDS could save: 503k points, 10 diameters, 168 us with every record from memory, 187 with all through
 // LDS, 165 with the wavefront's choice (in order: 130, 90 and 87).
-// CNN starts, in order and by XCD: 0.5M 20.3 and 18.0, 1M 36.7 and 33.2, 2M 77.2 and 76.4.  Looked-up starts go in
-// order again past 6,144 blocks, whose short walks have little left to share: 4M points 168.6 and 169.5, ASG starts 139
-// and 140.
+// Looked-up starts, CNN then overlay, 20 diameters, in us, in order and by XCD: 503k points 20.2 and 17.8, 18.3 and 15.9;
+// 1M 36.7 and 32.7, 32.4 and 28.6; 2.1M 97.9 and 97.6, 71.6 and 69.5.  They go in order again past 6,144 blocks, where
+// their short walks have little left to share: 3.4M (6,592 blocks) 92.2 and 90.2, 77.7 and 74.2; 4M 165 and 166, 136
+// and 138; 8M 310 and 310, 270 and 270; 8M in no order 678 and 679, 389 and 392.
 constexpr int64_t kSharedWaves = 2560;
 constexpr unsigned kOrderedBlocks = 6144;
 
